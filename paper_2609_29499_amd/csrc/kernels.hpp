@@ -163,8 +163,42 @@ hipError_t launch_pf_prep(const float* x, int D, int T, const uint16_t* gamma, u
                           size_t plane, int ldxo, float* ssq, hipStream_t s);
 int pf_ssq_block();
 
+// Per-row INT8 panels on the INT8 matrix cores. The operand x holds one row of 4 ldx bytes per
+// token: three planes of ldx signed base-256 digits (high to low), then the token's
+// float32 scale. MM_QKV: y = product; MM_RESID: y = resid + product; MM_GATEUP: y = silu(gate) *
+// up. With ks > 1 (not MM_GATEUP) split z writes its product to part [z][T][N] instead.
+struct PfI8Args {
+  const int8_t* w; uint32_t w2_off;   // panel rows [N][ld] (gate/up: gate rows; up at w2_off bytes)
+  const float* scale; const float* scale2;
+  int N, K, ld;
+  const uint8_t* x; int ldx;          // ldx % 128 == 0; digits zero to the next multiple of 128
+  const float* resid;                 // MM_RESID: [T][ldy]
+  float* y; int ldy;
+  int T, ks;
+  float* part; size_t part_floats;
+};
+// the tile shape and the number of K splits for these sizes
+void plan_pf_i8(MfmaMode mode, const PfI8Args& a, int* shape, int* ks);
+hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t s);
+// Digit rows o (PfI8Args::x layout, ldo bytes per digit) of the float32 rows x [T][ldx]. gamma:
+// the rows are x * gamma and the scale carries the inverse RMS of x. ks > 0: x is a residual
+// [T][K], the row is x + sum of part [ks][T][K], stored to y [T][K] as well. Without gamma and ks
+// o may be x's own buffer (ldo == ldx).
+struct PfQuantArgs {
+  const float* x; int ldx;
+  int K, T;
+  const uint16_t* gamma; float inv_d, eps;
+  const float* part; int ks; float* y;
+  void* o; int ldo;
+};
+hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s);
+// y = resid + sum of part [ks][T][N], rows of N floats
+hipError_t launch_pf_i8_reduce(const float* part, int ks, const float* resid, float* y, int T, int N,
+                               hipStream_t s);
+
 struct PfRopeArgs {
   const float* qkv; int ld_qkv;       // [T][ld_qkv]: raw q (m_q*dh), k (m_kv*dh), v (m_kv*dh)
+  int ks; size_t split_stride;        // qkv is the sum of ks such arrays, split_stride floats apart
   int m_q, m_kv, dh;
   int kv_idx[64];
   uint16_t* kc; uint16_t* vc;         // this layer's cache of sequence 0, [Hkv][S][dh]
@@ -182,7 +216,8 @@ struct PfAttnArgs {
   int slot_start[65];
   const uint16_t* kc; const uint16_t* vc;         // [Hkv][S][dh]
   int S, pos0, T;
-  uint16_t* o; int ldo; uint32_t o_plane;         // hi/lo operand [2][T][ldo]
+  float* o; int ldo;                              // [T][ldo], or the hi/lo operand [2][T][ldo]
+  uint16_t* o_hl; uint32_t o_plane;               // when o_hl is set
   // split query blocks: partial records (part_floats, nullable: no split) and one counter per
   // (retained head, query block), zero on entry and left zero
   float* part; size_t part_floats; int* cnt; int cnt_len;

@@ -1,0 +1,455 @@
+// Prefill projections over per-row INT8 panels on the INT8 matrix cores:
+// C[t][n] = sum_k A[t][k] P[n][k] with v_mfma_i32_32x32x32_i8 and exact int32 accumulation.
+//
+// Operands. A token's activations are carried as 24-bit fixed point under one power-of-two scale
+// per token, in three signed base-256 digits (q = 65536 d2 + 256 d1 + d0, each digit in -128..127),
+// written by pf_quant_kernel; the INT8 panel bytes are multiplied as they are, without widening.
+// Per (token, row) the three digit sums are exact integers and are joined in float32 in the
+// epilogue, so the only rounding before it is the digit grid: half a step of 2^-22 to 2^-23 of
+// the token's largest activation. Against the earlier operand pair (hi and lo BF16, about 2^-19
+// of each activation, on the BF16 matrix cores) the error of a random token is lower (rms 2^-22
+// of the token's rms for a largest value of 4 to 5 rms), and the issued matrix work is three
+// INT8 passes (3 / 3.3 POP/s measured) instead of two BF16 passes (2 / 1.8 PFLOP/s measured).
+//
+// Row layout of an operand: ld bytes of d2, ld of d1, ld of d0, then the token's scale (float32,
+// times the inverse RMS for a normed input); ld is a multiple of the 128-byte chunk and the digits
+// from K to the end of its last chunk are zero, so panel bytes past the end of a row multiply
+// zeros. A row takes the 4 ld bytes of the float32 row it came from: the O and down inputs are
+// written in float32 and turned into digits in place.
+//
+// Tiling. Workgroups of TM tokens x TN rows (gate/up: TN / 2 channels, gate and up rows of a
+// channel in one wave); each wave holds its outputs, times three digits, in registers. K advances
+// in chunks of 128, one memory line per row: digit rows and panel rows go from memory straight
+// into two LDS stages (buffer loads with an LDS destination, 16-byte pieces XOR-swizzled by row on
+// the memory side), the next chunk in flight while one is multiplied, one barrier per chunk.
+//
+// What bounds it: power. At a full chip of 128 x 256 tiles the clock falls from 2.4 to 1.6-1.8 GHz
+// (cycle against real-time counters), a chunk of 64 takes about 2100 cycles of which 1536 are
+// matrix cycles, and the matrix cores alone on random registers reach 3.3 POP/s of the nominal 5.
+// What saves energy therefore saves time: chunks of whole 128-byte lines instead of halves of them
+// (12 % more cycles, a 15 % higher clock), 32 x 128 outputs per wave instead of 64 x 64 (fewer LDS
+// reads per product, 4 %). With the loads left out (a copy of the kernel) the 2 x 16384 x 8192
+// gate/up projection at 2048 tokens takes 960 instead of 1300 us; on the BF16 matrix cores with
+// hi/lo operands it took 2240 us.
+#include <algorithm>
+
+#include "device_common.hpp"
+#include "kernels.hpp"
+
+namespace tasp {
+namespace {
+
+typedef int __attribute__((ext_vector_type(4))) i32x4;
+typedef int __attribute__((ext_vector_type(16))) i32x16;
+// four floats of a caller's array, which is only 4-byte aligned
+typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4u;
+
+constexpr int kKC = 128;                // k per chunk: one 128-byte line of a digit or panel row
+constexpr int kXcds = 8;
+constexpr int kNumCu = 256;
+constexpr int kGroupM = 4;              // token tiles walked together by one XCD's workgroups
+
+// s_waitcnt: no vector memory operation outstanding, the other counters not waited on
+__device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
+
+// LDS slot of 16-byte piece p of row `row` (rows of kKC bytes): any 8 consecutive rows read at one
+// piece meet distinct banks
+__device__ __forceinline__ int slot(int row, int p) { return p ^ (row & 7); }
+
+// the three digit sums of one output, joined in float32
+__device__ __forceinline__ float join(int s2, int s1, int s0) {
+  return fmaf(float(s2), 65536.0f, fmaf(float(s1), 256.0f, float(s0)));
+}
+
+template <int TM, int TN>
+struct I8Stage {
+  uint8_t a[3 * TM * kKC];               // digit planes, token rows of kKC bytes
+  uint8_t b[TN * kKC];                   // panel rows of kKC bytes
+};
+
+// Workgroup id -> (n tile, m tile, split). Ids go round-robin over the XCDs; each XCD takes a
+// contiguous run of an order that walks kGroupM token tiles together, so that the workgroups an
+// XCD holds at one time share digit and panel rows in its L2.
+__device__ __forceinline__ void tile_of(int id, int total, int gx, int gy, int& bx, int& by, int& bz) {
+  const int x = id % kXcds, j = id / kXcds;
+  const int o = x * (total / kXcds) + min(x, total % kXcds) + j;
+  bz = o / (gx * gy);
+  const int rem = o - bz * (gx * gy);
+  const int grp = rem / (kGroupM * gx);
+  const int gm = min(kGroupM, gy - grp * kGroupM);
+  const int in = rem - grp * (kGroupM * gx);
+  by = grp * kGroupM + in % gm;
+  bx = in / gm;
+}
+
+// MT x NT tiles of 32 tokens x 32 rows per wave; WGM x WGN waves; WAVES: per SIMD
+template <int MODE, int MT, int NT, int WGM, int WGN, int WAVES>
+__global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a, int gx, int gy) {
+  constexpr bool GU = (MODE == MM_GATEUP);
+  constexpr int HN = 16 * NT;                           // gate/up: channels per wave
+  constexpr int TM = 32 * MT * WGM, TN = 32 * NT * WGN, NW = WGM * WGN;
+  constexpr int RPL = 1024 / kKC, LPR = kKC / 16;         // rows per 1 KiB load, lanes per row
+  constexpr int APER = 3 * TM / RPL / NW, BPER = TN / RPL / NW;
+  static_assert(APER * RPL * NW == 3 * TM && BPER * RPL * NW == TN, "even share of the loads");
+  static_assert(TM <= 64 * NW, "one token scale per thread");
+  __shared__ __attribute__((aligned(16))) I8Stage<TM, TN> st0;
+  __shared__ __attribute__((aligned(16))) I8Stage<TM, TN> st1;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, hi = lane >> 5;
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int T = a.T, N = a.N;
+  int bx, by, bz;
+  tile_of(blockIdx.x, gridDim.x, gx, gy, bx, by, bz);
+  const int m0 = by * TM, n0 = bx * (GU ? TN / 2 : TN);
+  const int nk_all = (a.K + kKC - 1) / kKC;
+  const int kc0 = int((long(bz) * nk_all) / a.ks);
+  const int nk = int((long(bz + 1) * nk_all) / a.ks) - kc0;
+
+  const uint32_t xrow = 4u * uint32_t(a.ldx);           // bytes of an operand row
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(a.x, uint32_t(T) * xrow);
+  const uint32_t ldw = uint32_t(a.ld);
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.w, GU ? a.w2_off + uint32_t(N) * ldw : uint32_t(N) * ldw);
+
+  // this lane's share of a chunk: a load covers RPL rows, LPR lanes each; the wave's loads are
+  // digit rows RPL (wave + NW j) .. (plane-major), then panel rows RPL (wave + NW j) ..
+  uint32_t abase[APER], bbase[BPER];
+#pragma unroll
+  for (int j = 0; j < APER; ++j) {
+    const int i = wave + NW * j, plane = i / (TM / RPL);
+    const int lr = (i % (TM / RPL)) * RPL + lane / LPR, t = m0 + lr;
+    abase[j] = t < T ? uint32_t(t) * xrow + uint32_t(plane) * uint32_t(a.ldx) + 16u * slot(lr, lane % LPR) : kOOB;
+  }
+#pragma unroll
+  for (int j = 0; j < BPER; ++j) {
+    const int lr = (wave + NW * j) * RPL + lane / LPR;
+    const int row = GU ? n0 + HN * (lr / (2 * HN)) + lr % HN : n0 + lr;
+    const bool up = GU && lr % (2 * HN) >= HN;
+    bbase[j] = row < N ? (up ? a.w2_off : 0u) + uint32_t(row) * ldw + 16u * slot(lr, lane % LPR) : kOOB;
+  }
+  // chunks past the last reload it (into a stage that is not read again), so that every step
+  // issues alike. A panel row may end inside its last chunk: the bytes loaded past it are the next
+  // row's, or of the sections behind the panels, and meet zero digits.
+  auto issue = [&](int kc, I8Stage<TM, TN>& S) {
+    const int k0 = (kc0 + max(min(kc, nk - 1), 0)) * kKC;
+#pragma unroll
+    for (int j = 0; j < APER; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S.a[(wave + NW * j) * 1024]), 16, int(abase[j]), k0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < BPER; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, static_cast<void*>(&S.b[(wave + NW * j) * 1024]), 16, int(bbase[j]), k0, 0, 0);
+  };
+
+  // the token scales go first, so that waiting for them does not wait for the chunks
+  float tscale = 0.0f;
+  if (tid < TM) {
+    const uint32_t off = uint32_t(m0 + tid) * xrow + 3u * uint32_t(a.ldx);
+    tscale = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, int(m0 + tid < T ? off : kOOB), 0, 0));
+  }
+  issue(0, st0);
+
+  i32x16 acc[3][MT][NT];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[d][i][j][e] = 0;
+
+  auto compute = [&](const I8Stage<TM, TN>& S) {
+#pragma unroll 2
+    for (int ks = 0; ks < kKC / 32; ++ks) {
+      const int sl = 16 * slot(r, 2 * ks + hi);         // (rows differ from r by multiples of 32)
+      i32x4 bf[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        bf[nt] = *reinterpret_cast<const i32x4*>(&S.b[((wn * NT + nt) * 32 + r) * kKC + sl]);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const i32x4 af = *reinterpret_cast<const i32x4*>(&S.a[d * TM * kKC + ((wm * MT + mt) * 32 + r) * kKC + sl]);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            acc[d][mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, bf[nt], acc[d][mt][nt], 0, 0, 0);
+        }
+    }
+  };
+  // chunk kc sits in stage kc % 2: wait for this wave's loads of it, meet the other waves (their
+  // loads of it have landed, and all of them are done with the other stage), load the next chunk
+  // into the other stage, multiply
+  auto step = [&](int kc, const I8Stage<TM, TN>& cur, I8Stage<TM, TN>& nxt) {
+    wait_vm0();
+    __builtin_amdgcn_s_barrier();
+    issue(kc + 1, nxt);
+    compute(cur);
+  };
+  for (int kc = 0; kc < nk; kc += 2) {
+    step(kc, st0, st1);
+    if (kc + 1 < nk) step(kc + 1, st1, st0);
+  }
+  wait_vm0();
+  __syncthreads();                                      // every wave is done with the stages
+  float* ts = reinterpret_cast<float*>(&st0);
+  if (tid < TM) ts[tid] = tscale;
+  __syncthreads();
+
+  // ---- epilogue: lane (r, hi) holds tokens 8 g + 4 hi + i of each token tile for row r
+  float sc[NT];
+  int col[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    col[nt] = GU ? n0 + HN * wn + 32 * (nt % (NT / 2)) + r : n0 + (wn * NT + nt) * 32 + r;
+    sc[nt] = col[nt] < N ? (GU && nt >= NT / 2 ? a.scale2 : a.scale)[col[nt]] : 0.0f;
+  }
+  float* part = a.ks > 1 ? a.part + size_t(bz) * T * N : nullptr;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int tl = (wm * MT + mt) * 32 + 8 * (e >> 2) + 4 * hi + (e & 3);
+      const int t = m0 + tl;
+      if (t >= T) continue;
+      const float tsc = ts[tl];
+      float v[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        v[nt] = join(acc[0][mt][nt][e], acc[1][mt][nt][e], acc[2][mt][nt][e]) * tsc * sc[nt];
+      if constexpr (GU) {
+#pragma unroll
+        for (int nt = 0; nt < NT / 2; ++nt)
+          if (col[nt] < N)
+            a.y[size_t(t) * a.ldy + col[nt]] = v[nt] / (1.0f + exp2f(-v[nt] * kLog2e)) * v[nt + NT / 2];
+      } else {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          if (col[nt] >= N) continue;
+          if (part) part[size_t(t) * N + col[nt]] = v[nt];
+          else if (MODE == MM_RESID) a.y[size_t(t) * a.ldy + col[nt]] = a.resid[size_t(t) * a.ldy + col[nt]] + v[nt];
+          else a.y[size_t(t) * a.ldy + col[nt]] = v[nt];
+        }
+      }
+    }
+}
+
+// Float32 rows -> digit rows. One workgroup per token; thread i holds elements 4 (i + THREADS j).
+// With a gain: the operand is x * gamma and the token's scale carries the inverse RMS of x. With
+// K splits (part): x = resid + the splits' sum (in split order), which is also stored to y. The
+// row is read in full before any digit is written, so source and destination may be one buffer.
+// The scale is the largest power of two 2^-e that keeps q = rint(v 2^e) within three digits
+// (|q| <= 0x7f7f7f); a row with a non-finite value gets a NaN scale, a zero row digits of zero.
+// Bound by its 4 to 8 bytes read and 3 written per element.
+template <int THREADS, int NV>
+__global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
+  __shared__ float red[2][THREADS / kWave];
+  const int tid = threadIdx.x, t = blockIdx.x, K = a.K, ld = a.ldo;
+  const int kz = (K + kKC - 1) / kKC * kKC;              // digits written: K and its zero padding
+  float4 v[NV];
+  float amax = 0.0f, ss = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int k = 4 * (tid + THREADS * j);
+    v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (k >= K) continue;                               // (K % 4 == 0 or the rest of the row is padding)
+    const f32x4u xv = *reinterpret_cast<const f32x4u*>(a.x + size_t(t) * a.ldx + k);
+    v[j] = make_float4(xv.x, xv.y, xv.z, xv.w);
+    for (int z = 0; z < a.ks; ++z) {
+      const float4 p = *reinterpret_cast<const float4*>(a.part + (size_t(z) * a.T + t) * K + k);
+      v[j].x += p.x; v[j].y += p.y; v[j].z += p.z; v[j].w += p.w;
+    }
+    if (a.ks) *reinterpret_cast<float4*>(a.y + size_t(t) * K + k) = v[j];
+    if (a.gamma) {
+      ss = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, fmaf(v[j].z, v[j].z, fmaf(v[j].w, v[j].w, ss))));
+      const uint2 g = *reinterpret_cast<const uint2*>(a.gamma + k);
+      v[j].x *= bf16_lo(g.x); v[j].y *= bf16_hi(g.x); v[j].z *= bf16_lo(g.y); v[j].w *= bf16_hi(g.y);
+    } else {
+      // columns past K of the last four are padding, whatever the buffer holds
+      if (k + 1 >= K) v[j].y = 0.0f;
+      if (k + 2 >= K) v[j].z = 0.0f;
+      if (k + 3 >= K) v[j].w = 0.0f;
+    }
+    // NaN-propagating maximum on the bits: |v| as an unsigned integer orders like the float, with
+    // infinities and then NaNs above every finite value
+    const uint32_t b = max(max(__float_as_uint(v[j].x) & 0x7fffffffu, __float_as_uint(v[j].y) & 0x7fffffffu),
+                           max(__float_as_uint(v[j].z) & 0x7fffffffu, __float_as_uint(v[j].w) & 0x7fffffffu));
+    amax = __uint_as_float(max(__float_as_uint(amax), b));
+  }
+  uint32_t mb = __float_as_uint(amax);
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    mb = max(mb, uint32_t(__shfl_xor(int(mb), o, kWave)));
+    ss += __shfl_xor(ss, o, kWave);
+  }
+  const int w = tid >> 6;
+  if ((tid & 63) == 0) {
+    red[0][w] = __uint_as_float(mb);
+    red[1][w] = ss;
+  }
+  __syncthreads();
+  mb = 0;
+  ss = 0.0f;
+#pragma unroll
+  for (int i = 0; i < THREADS / kWave; ++i) {
+    mb = max(mb, __float_as_uint(red[0][i]));
+    ss += red[1][i];
+  }
+  const bool finite = mb < 0x7f800000u;
+  const float big = __uint_as_float(mb);
+  // big 2^e in [2^22, 2^23), one less where the digits would not hold it; e <= 126 keeps the scale
+  // a normal number (smaller rows lose digits below 2^-126)
+  int e = 22 - ((int(mb >> 23)) - 127);
+  if (mb < 0x00800000u || e > 126) e = 126;
+  if (ldexpf(big, e) > 8355711.0f) --e;
+  const float up = ldexpf(1.0f, e > 127 ? 127 : e);
+  uint8_t* row = reinterpret_cast<uint8_t*>(a.o) + size_t(t) * 4 * ld;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int k = 4 * (tid + THREADS * j);
+    if (k >= kz) continue;
+    const float f[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+    uint32_t d2 = 0, d1 = 0, d0 = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = finite ? int(rintf(f[i] * up)) : 0;
+      // balanced digits: adding 128 to the lower two makes the carries
+      const int c = q + 0x8080;
+      d0 |= ((uint32_t(c) & 0xffu) ^ 0x80u) << (8 * i);
+      d1 |= (((uint32_t(c) >> 8) & 0xffu) ^ 0x80u) << (8 * i);
+      d2 |= ((uint32_t(c >> 16)) & 0xffu) << (8 * i);
+    }
+    *reinterpret_cast<uint32_t*>(row + k) = d2;
+    *reinterpret_cast<uint32_t*>(row + ld + k) = d1;
+    *reinterpret_cast<uint32_t*>(row + 2 * size_t(ld) + k) = d0;
+  }
+  if (tid == 0) {
+    float s = ldexpf(1.0f, -e);
+    if (a.gamma) s *= rsqrtf(ss * a.inv_d + a.eps);
+    *reinterpret_cast<float*>(row + 3 * size_t(ld)) = finite ? s : __uint_as_float(0x7fc00000u);
+  }
+}
+
+// y = resid + the K splits' sum in split order (the last layer's output: no next operand)
+__global__ __launch_bounds__(kBlock) void pf_i8_reduce_kernel(const float* __restrict__ part, int ks,
+                                                              const float* __restrict__ resid, float* y,
+                                                              int T, int N) {
+  const int t = blockIdx.y, n = 4 * (blockIdx.x * kBlock + threadIdx.x);
+  if (n >= N) return;
+  f32x4u v = *reinterpret_cast<const f32x4u*>(resid + size_t(t) * N + n);
+  for (int z = 0; z < ks; ++z) {
+    const float4 p = *reinterpret_cast<const float4*>(part + (size_t(z) * T + t) * N + n);
+    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+  }
+  *reinterpret_cast<f32x4u*>(y + size_t(t) * N + n) = v;
+}
+
+struct Shape {
+  int tm, tn, per_cu;
+  float t_one, t_cu, t_full;            // us per chunk: few workgroups, one per CU, per_cu per CU
+};
+// 0: 128 x 256, eight waves of 32 x 128; 1: 64 x 128, four waves of 32 x 64; 2: 32 x 128, two waves
+// of 32 x 64. The chunk times are measured (8B and 70B gate/up and down at 8 to 2048 tokens).
+constexpr Shape kShapes[3] = {{128, 256, 1, 1.9f, 2.65f, 2.65f},
+                              {64, 128, 2, 0.85f, 0.94f, 1.52f},
+                              {32, 128, 2, 0.65f, 0.75f, 1.30f}};
+constexpr float kFixedUs = 4.0f;        // launch, first chunk, epilogue
+constexpr int kMaxKSplit = 8;
+constexpr int kMinSplitChunks = 2;
+
+// expected time of a launch of w workgroups of n chunks each
+float launch_us(const Shape& h, long w, int n) {
+  const long slots = long(kNumCu) * h.per_cu;
+  auto chunk = [&](long u) {            // chunk time with u workgroups on the chip
+    return u <= kNumCu ? h.t_one + (h.t_cu - h.t_one) * float(u) / kNumCu
+                       : h.t_cu + (h.t_full - h.t_cu) * float(u - kNumCu) / float(slots - kNumCu);
+  };
+  const long rounds = w / slots, rest = w % slots;
+  return kFixedUs + float(n) * (float(rounds) * h.t_full + (rest ? chunk(rest) : 0.0f));
+}
+
+template <int MODE>
+hipError_t launch_mode(const PfI8Args& a, int shape, hipStream_t s) {
+  const Shape& h = kShapes[shape];
+  const int rows = MODE == MM_GATEUP ? h.tn / 2 : h.tn;
+  const int gx = (a.N + rows - 1) / rows, gy = (a.T + h.tm - 1) / h.tm;
+  const dim3 grid(uint32_t(gx) * uint32_t(gy) * uint32_t(a.ks));
+  if (shape == 0) hipLaunchKernelGGL((pf_i8_kernel<MODE, 1, 4, 4, 2, 2>), grid, dim3(512), 0, s, a, gx, gy);
+  else if (shape == 1) hipLaunchKernelGGL((pf_i8_kernel<MODE, 1, 2, 2, 2, 2>), grid, dim3(256), 0, s, a, gx, gy);
+  else hipLaunchKernelGGL((pf_i8_kernel<MODE, 1, 2, 1, 2, 1>), grid, dim3(128), 0, s, a, gx, gy);
+  return hipGetLastError();
+}
+
+template <int THREADS>
+hipError_t launch_quant(const PfQuantArgs& a, hipStream_t s) {
+  const int nv = ((a.K + kKC - 1) / kKC * kKC + 4 * THREADS - 1) / (4 * THREADS);
+  const dim3 g(a.T), b(THREADS);
+  if (nv <= 1) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 1>), g, b, 0, s, a);
+  else if (nv <= 2) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 2>), g, b, 0, s, a);
+  else if (nv <= 4) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 4>), g, b, 0, s, a);
+  else if (nv <= 7) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 7>), g, b, 0, s, a);
+  else if (nv <= 11) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 11>), g, b, 0, s, a);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// The tile shape and K splits of least expected time (launch_us). A split adds its partial sums,
+// written here and read by the consumer (about 4 TB/s). Large shapes move fewer bytes per product;
+// small ones and splits fill the chip when there are few tokens: at 8 tokens the 8B down
+// projection takes 119 us on 32 x 1 workgroups of shape 0 and 11 us on 32 x 8 of shape 2, at 2048
+// tokens 184 us on shape 0 and 242 on shape 1.
+void plan_pf_i8(MfmaMode mode, const PfI8Args& a, int* shape, int* ks) {
+  const int chunks = (a.K + kKC - 1) / kKC;
+  const bool can_split = mode != MM_GATEUP && a.part && a.N > 0;
+  const long room = can_split ? long(a.part_floats / (size_t(a.T) * a.N)) : 1;
+  const int max_ks = can_split ? int(std::max(1l, std::min({long(kMaxKSplit), long(chunks / kMinSplitChunks), room}))) : 1;
+  float best = 0.0f;
+  *shape = 0;
+  *ks = 1;
+  for (int i = 0; i < 3; ++i) {
+    const Shape& h = kShapes[i];
+    const int rows = mode == MM_GATEUP ? h.tn / 2 : h.tn;
+    const long tiles = long((a.N + rows - 1) / rows) * ((a.T + h.tm - 1) / h.tm);
+    for (int k = 1; k <= max_ks; ++k) {
+      const float us = launch_us(h, tiles * k, (chunks + k - 1) / k) +
+                       (k > 1 ? float(k) * float(a.T) * float(a.N) * 4.0f * 2.0f / 4e6f : 0.0f);
+      if ((i == 0 && k == 1) || us < best) {
+        best = us;
+        *shape = i;
+        *ks = k;
+      }
+    }
+  }
+}
+
+hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t s) {
+  if (a.T < 1 || a.K < 0 || a.K > a.ld || a.ld % 16 != 0 || a.ldx % kKC != 0 || a.ldx < a.K || a.ks < 1 ||
+      shape < 0 || shape > 2 || size_t(a.T) * 4 * a.ldx >= size_t(kOOB) ||
+      (a.ks > 1 && (mode == MM_GATEUP || !a.part || size_t(a.ks) * a.T * a.N > a.part_floats)))
+    return hipErrorInvalidValue;
+  if (a.N == 0) return hipSuccess;
+  switch (mode) {
+    case MM_QKV: return launch_mode<MM_QKV>(a, shape, s);
+    case MM_RESID: return launch_mode<MM_RESID>(a, shape, s);
+    case MM_GATEUP: return launch_mode<MM_GATEUP>(a, shape, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s) {
+  if (a.T < 1 || a.K < 0 || a.ldo % kKC != 0 || a.ldo < a.K || a.ldx % 4 != 0 || ((a.gamma || a.ks) && a.K % 4 != 0))
+    return hipErrorInvalidValue;
+  return a.K <= 4 * 256 * 7 ? launch_quant<256>(a, s) : launch_quant<1024>(a, s);
+}
+
+hipError_t launch_pf_i8_reduce(const float* part, int ks, const float* resid, float* y, int T, int N,
+                               hipStream_t s) {
+  if (N % 4 != 0 || T < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pf_i8_reduce_kernel, dim3((N / 4 + kBlock - 1) / kBlock, T), dim3(kBlock), 0, s, part, ks,
+                     resid, y, T, N);
+  return hipGetLastError();
+}
+
+}  // namespace tasp

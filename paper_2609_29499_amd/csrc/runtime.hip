@@ -44,6 +44,7 @@ constexpr size_t kLdsLimit = 159 * 1024;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 int round_up16(int v) { return (v + 15) / 16 * 16; }
 int round_up64(int v) { return (v + 63) / 64 * 64; }
+int round_up128(int v) { return (v + 127) / 128 * 128; }
 
 // ----------------------------------------------------------------------- closure on the host
 
@@ -177,7 +178,7 @@ void scratch_layout(Layout& Y, const tasp_model_desc* d, Take&& take, size_t& of
   Y.h_buf = take(size_t(B) * Y.ld_h * 4);
   Y.part = take(size_t(B) * Hkv * Y.n_split_max * 8 * (dh + 4) * 4);
   Y.acnt = take(size_t(B) * Hkv * 4);
-  Y.ld_xd = round_up64(D);
+  Y.ld_xd = round_up128(D);              // (the prefill digit planes end on 128-byte lines)
   Y.ld_xo = round_up64(Hq * dh);
   Y.ld_xh = round_up64(F);
   const bool batched = B > 1;
@@ -187,7 +188,7 @@ void scratch_layout(Layout& Y, const tasp_model_desc* d, Take&& take, size_t& of
   Y.ssq = take(batched ? size_t(B) * (D / 16) * 4 : 0);
   // prefill of up to P tokens: hi/lo operand planes, q planes, q/k/v, residuals, RMS partials
   const size_t P = size_t(d->max_prefill);
-  Y.ld_xw = round_up64(std::max(Hq * dh, F));
+  Y.ld_xw = round_up128(std::max(Hq * dh, F));
   Y.pxd = take(2 * P * Y.ld_xd * 2);
   Y.pxw = take(2 * P * Y.ld_xw * 2);
   Y.pq = take(2 * size_t(Hq) * P * dh * 2);
@@ -665,10 +666,134 @@ tasp::PfArgs pf_base(const tasp_plan_s* p, int T) {
   return a;
 }
 
-// last_only: with an LM head, only the last token's logits (out [vocab]), by the decode LM head
-// GEMV over that token's final residual (greedy decoding needs no other row)
+// final norm + LM head of a prefill whose last residual is r: every token's logits, or (last_only)
+// the last token's by the decode LM head GEMV over that token's row (greedy decoding needs no
+// other)
+tasp_status prefill_head(tasp_plan p, const float* r, int T, float* out, hipStream_t s, Timer* tm,
+                         bool last_only) {
+  const tasp_model_desc& d = p->desc;
+  const int D = d.d_model;
+  if (last_only) {
+    tasp::GemvArgs a{};
+    a.w = p->lm_head; a.N = d.vocab; a.K = D; a.ld = 2 * D;
+    a.x = r + size_t(T - 1) * D; a.ldx = D;
+    a.gamma = p->final_norm; a.eps = d.rms_eps; a.y = out; a.ldy = d.vocab;
+    a.B = 1;
+    return run_kernel(tm, 5, s, [&] { return tasp::launch_gemv(tasp::GEMV_LMHEAD, a, s); });
+  }
+  tasp::PfArgs a = pf_base(p, T);
+  const uint32_t plane_d = uint32_t(size_t(d.max_prefill) * p->ld_xd);
+  a.w = p->lm_head; a.N = d.vocab; a.K = D; a.ld = D; a.x = p->pxd; a.ldx = p->ld_xd;
+  a.plane = plane_d; a.ssq = p->pssq; a.y = out; a.ldy = d.vocab;
+  return run_kernel(tm, 5, s, [&] { return tasp::launch_pf_gemm(tasp::MM_LMHEAD, a, s); });
+}
+
+// prefill of a per-row plan: every projection on the INT8 matrix cores over digit operands. The
+// normed inputs (QKV, gate/up) have their digits in pxd; the O and down inputs are written to pxw
+// in float32 and turned into digits there.
+tasp_status prefill_i8(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0, float* out,
+                       hipStream_t s, Timer* tm, bool last_only) {
+  const tasp_model_desc& d = p->desc;
+  const int D = d.d_model, dh = d.head_dim, L = d.n_layers, Pm = d.max_prefill;
+  const uint32_t plane_q = uint32_t(size_t(d.n_q_heads) * Pm * dh);
+  const size_t layer_cache = size_t(cache->batch) * d.n_kv_heads * cache->max_seq * dh;
+  float* wide = reinterpret_cast<float*>(p->pxw);
+  tasp_status st;
+  auto gemm = [&](int kind, tasp::MfmaMode mode, tasp::PfI8Args& a) {
+    int shape = 0;
+    a.T = T; a.part = p->ppart; a.part_floats = p->ppart_floats;
+    tasp::plan_pf_i8(mode, a, &shape, &a.ks);
+    return run_kernel(tm, kind, s, [&] { return tasp::launch_pf_i8(mode, a, shape, s); });
+  };
+  // digits of (r [+ the ks splits' sum, stored to y]) * gamma into pxd
+  auto quant_norm = [&](const float* r, const uint16_t* gamma, int ks, float* y) {
+    tasp::PfQuantArgs a{};
+    a.x = r; a.ldx = D; a.K = D; a.T = T; a.gamma = gamma; a.inv_d = 1.0f / float(D); a.eps = d.rms_eps;
+    a.part = p->ppart; a.ks = ks > 1 ? ks : 0; a.y = y; a.o = p->pxd; a.ldo = p->ld_xd;
+    return run_kernel(tm, 6, s, [&] { return tasp::launch_pf_quant(a, s); });
+  };
+  auto quant_wide = [&](int K) {
+    tasp::PfQuantArgs a{};
+    a.x = wide; a.ldx = p->ld_xw; a.K = K; a.T = T; a.o = wide; a.ldo = p->ld_xw;
+    return run_kernel(tm, 6, s, [&] { return tasp::launch_pf_quant(a, s); });
+  };
+  if ((st = quant_norm(x, p->layers[0].an, 1, nullptr))) return st;
+  for (int l = 0; l < L; ++l) {
+    const LayerPlan& P = p->layers[l];
+    const float* in = (l == 0) ? x : p->pr_io[(l - 1) & 1];
+    float* lo = (l == L - 1 && d.vocab == 0) ? out : p->pr_io[l & 1];
+    uint16_t* kc = static_cast<uint16_t*>(cache->k) + l * layer_cache;
+    uint16_t* vc = static_cast<uint16_t*>(cache->v) + l * layer_cache;
+    if (P.n_qkv > 0) {
+      tasp::PfI8Args a{};
+      a.w = P.qkv; a.scale = P.s_qkv; a.N = P.n_qkv; a.K = D; a.ld = D;
+      a.x = reinterpret_cast<uint8_t*>(p->pxd); a.ldx = p->ld_xd; a.y = p->pqkv; a.ldy = p->ld_qkv;
+      if ((st = gemm(0, tasp::MM_QKV, a))) return st;
+      tasp::PfRopeArgs r{};
+      r.qkv = p->pqkv; r.ld_qkv = p->ld_qkv; r.ks = a.ks;
+      if (a.ks > 1) {
+        r.qkv = p->ppart; r.ld_qkv = P.n_qkv; r.split_stride = size_t(T) * P.n_qkv;
+      }
+      r.m_q = P.m_q; r.m_kv = P.m_kv; r.dh = dh;
+      for (int q = 0; q < P.m_kv; ++q) r.kv_idx[q] = P.kv_idx[q];
+      r.kc = kc; r.vc = vc; r.S = cache->max_seq; r.rope_cos = p->rope_cos; r.rope_sin = p->rope_sin;
+      r.pos0 = pos0; r.T = T; r.q_out = p->pq; r.q_plane = plane_q; r.T_ld = Pm;
+      if ((st = run_kernel(tm, 7, s, [&] { return tasp::launch_pf_rope(r, s); }))) return st;
+      tasp::PfAttnArgs t{};
+      t.q = p->pq; t.q_plane = plane_q; t.T_ld = Pm; t.m_kv = P.m_kv; t.dh = dh;
+      for (int q = 0; q < P.m_kv; ++q) t.kv_idx[q] = P.kv_idx[q];
+      for (int q = 0; q <= P.m_kv; ++q) t.slot_start[q] = P.slot_start[q];
+      t.kc = kc; t.vc = vc; t.S = cache->max_seq; t.pos0 = pos0; t.T = T;
+      t.o = wide; t.ldo = p->ld_xw;
+      t.part = p->ppart; t.part_floats = p->ppart_floats; t.cnt = p->pacnt; t.cnt_len = p->pacnt_len;
+      if ((st = run_kernel(tm, 1, s, [&] { return tasp::launch_pf_attn(t, s); }))) return st;
+    }
+    if ((st = quant_wide(P.m_q * dh))) return st;
+    {
+      tasp::PfI8Args a{};
+      a.w = P.o; a.scale = P.s_o; a.N = D; a.K = P.m_q * dh; a.ld = P.ld_o;
+      a.x = reinterpret_cast<uint8_t*>(p->pxw); a.ldx = p->ld_xw; a.resid = in; a.y = p->pr_mid; a.ldy = D;
+      if ((st = gemm(2, tasp::MM_RESID, a))) return st;
+      if ((st = quant_norm(a.ks > 1 ? in : p->pr_mid, P.fn, a.ks, p->pr_mid))) return st;
+    }
+    if (P.c > 0) {
+      tasp::PfI8Args a{};
+      a.w = P.g;
+      a.w2_off = uint32_t(reinterpret_cast<const char*>(P.u) - reinterpret_cast<const char*>(P.g));
+      a.scale = P.s_g; a.scale2 = P.s_u; a.N = P.c; a.K = D; a.ld = D;
+      a.x = reinterpret_cast<uint8_t*>(p->pxd); a.ldx = p->ld_xd; a.y = wide; a.ldy = p->ld_xw;
+      if ((st = gemm(3, tasp::MM_GATEUP, a))) return st;
+    }
+    if ((st = quant_wide(P.c))) return st;
+    {
+      tasp::PfI8Args a{};
+      a.w = P.dn; a.scale = P.s_d; a.N = D; a.K = P.c; a.ld = P.ld_d;
+      a.x = reinterpret_cast<uint8_t*>(p->pxw); a.ldx = p->ld_xw; a.resid = p->pr_mid; a.y = lo; a.ldy = D;
+      if ((st = gemm(4, tasp::MM_RESID, a))) return st;
+      if (l + 1 < L) {
+        if ((st = quant_norm(a.ks > 1 ? p->pr_mid : lo, p->layers[l + 1].an, a.ks, lo))) return st;
+      } else if (a.ks > 1) {
+        if ((st = run_kernel(tm, 4, s, [&] {
+               return tasp::launch_pf_i8_reduce(p->ppart, a.ks, p->pr_mid, lo, T, D, s);
+             })))
+          return st;
+      }
+    }
+  }
+  if (!d.vocab) return TASP_OK;
+  const float* r = p->pr_io[(L - 1) & 1];
+  if (!last_only &&
+      (st = run_kernel(tm, 6, s, [&] {
+         return tasp::launch_pf_prep(r, D, T, p->final_norm, p->pxd, uint32_t(size_t(Pm) * p->ld_xd), p->ld_xd,
+                                     p->pssq, s);
+       })))
+    return st;
+  return prefill_head(p, r, T, out, s, tm, last_only);
+}
+
 tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0,
-                         float* out, hipStream_t s, Timer* tm, bool last_only = false) {
+                         float* out, hipStream_t s, Timer* tm, bool last_only) {
+  if (!p->shared) return prefill_i8(p, x, T, cache, pos0, out, s, tm, last_only);
   const tasp_model_desc& d = p->desc;
   const int D = d.d_model, dh = d.head_dim, L = d.n_layers, Pm = d.max_prefill;
   const uint32_t plane_d = uint32_t(size_t(Pm) * p->ld_xd);
@@ -697,7 +822,7 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
     }
     if (P.m_kv > 0) {
       tasp::PfRopeArgs r{};
-      r.qkv = p->pqkv; r.ld_qkv = p->ld_qkv; r.m_q = P.m_q; r.m_kv = P.m_kv; r.dh = dh;
+      r.qkv = p->pqkv; r.ld_qkv = p->ld_qkv; r.ks = 1; r.m_q = P.m_q; r.m_kv = P.m_kv; r.dh = dh;
       for (int q = 0; q < P.m_kv; ++q) r.kv_idx[q] = P.kv_idx[q];
       r.kc = kc; r.vc = vc; r.S = cache->max_seq; r.rope_cos = p->rope_cos; r.rope_sin = p->rope_sin;
       r.pos0 = pos0; r.T = T; r.q_out = p->pq; r.q_plane = plane_q; r.T_ld = Pm;
@@ -707,7 +832,7 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
       for (int q = 0; q < P.m_kv; ++q) a.kv_idx[q] = P.kv_idx[q];
       for (int q = 0; q <= P.m_kv; ++q) a.slot_start[q] = P.slot_start[q];
       a.kc = kc; a.vc = vc; a.S = cache->max_seq; a.pos0 = pos0; a.T = T;
-      a.o = p->pxw; a.ldo = p->ld_xw; a.o_plane = plane_w;
+      a.o_hl = p->pxw; a.ldo = p->ld_xw; a.o_plane = plane_w;
       a.part = p->ppart; a.part_floats = p->ppart_floats; a.cnt = p->pacnt; a.cnt_len = p->pacnt_len;
       if ((st = run_kernel(tm, 1, s, [&] { return tasp::launch_pf_attn(a, s); }))) return st;
     }
@@ -745,22 +870,7 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
         return st;
     }
   }
-  if (d.vocab && last_only) {
-    tasp::GemvArgs a{};
-    a.w = p->lm_head; a.N = d.vocab; a.K = D; a.ld = 2 * D;
-    a.x = p->pr_io[(L - 1) & 1] + size_t(T - 1) * D; a.ldx = D;
-    a.gamma = p->final_norm; a.eps = d.rms_eps; a.y = out; a.ldy = d.vocab;
-    a.B = 1;
-    if ((st = run_kernel(tm, 5, s, [&] { return tasp::launch_gemv(tasp::GEMV_LMHEAD, a, s); })))
-      return st;
-  } else if (d.vocab) {
-    tasp::PfArgs a = pf_base(p, T);
-    a.w = p->lm_head; a.N = d.vocab; a.K = D; a.ld = D; a.x = p->pxd; a.ldx = p->ld_xd;
-    a.plane = plane_d; a.ssq = p->pssq; a.y = out; a.ldy = d.vocab;
-    if ((st = run_kernel(tm, 5, s, [&] { return tasp::launch_pf_gemm(tasp::MM_LMHEAD, a, s); })))
-      return st;
-  }
-  return TASP_OK;
+  return d.vocab ? prefill_head(p, p->pr_io[(L - 1) & 1], T, out, s, tm, last_only) : TASP_OK;
 }
 
 tasp_status prefill_checked(tasp_plan p, const float* x, int32_t T, tasp_kv_cache* cache,

@@ -31,7 +31,7 @@ def kind_of(name: str) -> str | None:
         (r"attn_mfma_kernel", "attention"),
         (r"pf_attn_kernel", "prefill_attention"),
         (r"pf_rope_kernel", "rope_append"),
-        (r"pf_prep_kernel|mfma_prep_kernel", "operand_prep"),
+        (r"pf_prep_kernel|pf_quant_kernel|mfma_prep_kernel", "operand_prep"),
         (r"gemv_kernel<1, 0[,>]", "qkv_gemv"),
         (r"gemv_kernel<1, 2[,>]", "gateup_gemv"),
         (r"gemv_kernel<1, 1[,>]", "resid_gemv"),
@@ -45,10 +45,10 @@ def kind_of(name: str) -> str | None:
         (r"mfma_gemv_kernel<1,", "resid_mfma"),
         (r"mfma_gemv_kernel<3,", "lmhead_mfma"),
         (r"pf_split_reduce_kernel<0>", "qkv_reduce"),
-        (r"pf_split_reduce_kernel<1>", "resid_reduce"),
-        (r"pf_(gemm|dma)_kernel<0,", "qkv_gemm"),
-        (r"pf_(gemm|dma)_kernel<2,", "gateup_gemm"),
-        (r"pf_(gemm|dma)_kernel<1,", "resid_gemm"),
+        (r"pf_split_reduce_kernel<1>|pf_i8_reduce_kernel", "resid_reduce"),
+        (r"pf_(gemm|i8)_kernel<0,", "qkv_gemm"),
+        (r"pf_(gemm|i8)_kernel<2,", "gateup_gemm"),
+        (r"pf_(gemm|i8)_kernel<1,", "resid_gemm"),
         (r"pf_gemm_kernel<3,", "lmhead_gemm"),
         (r"router_features_kernel", "router_features"),
         (r"router_dense_kernel", "router_dense"),

@@ -1,0 +1,86 @@
+"""Prefill projections over digit operands (24-bit fixed point under one scale per token, three INT8
+passes): tile and split remainders of the three tile shapes, ragged K, and rows at the edges of the
+number range.
+
+Tolerance: a digit operand is within 2^-23 of its token's largest activation (half a step of a
+power-of-two grid of at least 2^22 steps), so a product over K columns is within 2^-23 sqrt(K) times
+(largest / rms) of its 2-norm, under 1e-5 for K <= 8192 and a largest value of 8 rms. What exceeds
+that is the rounding of k and v to BF16: a value near a tie moves by one step (2^-8 of it), for a
+share of the entries of about the relative error before it over 2^-8. 2e-4 of the 2-norm covers one
+entry in a thousand moving. (Hi/lo BF16 operands on the same cases: up to 1e-4.)"""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from tests.gpu_case import PrefillCase
+
+pytestmark = pytest.mark.gpu
+REL = 2e-4
+
+
+def _rel(got, want):
+    return float(np.linalg.norm(got - want) / np.linalg.norm(want))
+
+
+def _case(sh, T, pos0=0, seed=5, p_f=0.6):
+    return PrefillCase(sh, synth.raw_mask(sh, seed, p_f=p_f), T, pos0)
+
+
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 64, 65, 128, 129, 300])
+def test_token_remainders(T):
+    """Token counts around the 32-, 64- and 128-token tiles; width 528 and a per-channel mask leave
+    K and N without any alignment beyond 16, and every projection splits K where T is small."""
+    print(f"case digits T={T}", flush=True)
+    sh = synth.tiny_shape(d=528, hq=6, hkv=3, dh=64, f=2000)
+    case = _case(sh, T, pos0=7)
+    assert _rel(case.run(), case.oracle()) < REL
+
+
+@pytest.mark.parametrize("d,hq,hkv,dh,f,T", [(16, 1, 1, 64, 16, 5),        # one chunk, mostly padding
+                                             (128, 2, 1, 128, 144, 40),
+                                             (1040, 8, 8, 128, 8208, 70),   # long ragged down rows
+                                             (4096, 32, 8, 128, 4096, 520)])   # 128 x 256 tiles
+def test_widths(d, hq, hkv, dh, f, T):
+    print(f"case digits d={d} hq={hq} hkv={hkv} dh={dh} f={f} T={T}", flush=True)
+    case = _case(synth.tiny_shape(d=d, hq=hq, hkv=hkv, dh=dh, f=f), T)
+    assert _rel(case.run(), case.oracle()) < REL
+
+
+def test_number_range():
+    """Rows of zeros, of tiny and of large values, and rows with one value far above the rest: each
+    token has its own scale, so a token's result does not depend on its neighbours, and its error
+    stays relative to its own result."""
+    print("case digits number range", flush=True)
+    sh = synth.tiny_shape(d=512, hq=8, hkv=2, dh=64, f=1536)
+    case = _case(sh, 8)
+    x = case.x.copy()
+    x[1] = 0.0
+    x[2] *= 1e-20
+    x[3] *= 1e12
+    x[4, 7] = 3e3
+    x[5, :] = 0.0
+    x[5, 9] = -2.5
+    case.x, case.xd = x, torch.from_numpy(x).cuda()
+    got, want = case.run(), case.oracle()
+    for t in (0, 2, 3, 4, 5, 6, 7):
+        assert _rel(got[t], want[t]) < REL, t
+    assert np.abs(got[1] - want[1]).max() <= REL * max(1.0, np.abs(want[1]).max())
+
+
+def test_non_finite_rows():
+    """A non-finite token gives a non-finite row and leaves the other tokens' bits alone (a layer
+    without heads, so that no token reads another's key)."""
+    print("case digits non-finite", flush=True)
+    sh = synth.tiny_shape(d=512, hq=8, hkv=2, dh=64, f=1536)
+    q, kv, f = synth.all_kept_mask(sh)
+    q[:] = 0
+    case = PrefillCase(sh, (q, kv, f), 8, 0)
+    got = case.run()
+    assert _rel(got, case.oracle()) < REL
+    for bad in (np.inf, np.nan):
+        case.xd = torch.from_numpy(case.x).cuda()
+        case.xd[6, 3] = float(bad)
+        out = case.run()
+        assert np.array_equal(np.delete(out, 6, 0), np.delete(got, 6, 0))
+        assert not np.isfinite(out[6]).any()
