@@ -136,25 +136,18 @@ hipError_t launch_mfma_prep(const float* x, int ldx, int D, const uint16_t* gamm
 
 // ----------------------------------------------------------------- prefill on MFMA
 
-// T tokens of one sequence. Activation operands are two BF16 planes (hi, lo) of [T][ldx] each,
-// `plane` elements apart; modes as for the batched decode. The inverse RMS of token t is
-// rsqrt(inv_d * sum(ssq[t][0..n_ssq)) + eps) when ssq is given (partials per 64 rows).
-struct PfArgs {
-  const void* w; uint32_t w2_off;     // panel rows [N][ld] (gate/up: gate rows; up at w2_off bytes)
-  const float* scale; const float* scale2;
-  int N, K, ld;
+// The BF16 LM head over T tokens: y[t][n] = w[n] . x[t]. The operand is two BF16 planes (hi, lo) of
+// [T][ldx] each, `plane` elements apart. The inverse RMS of token t is
+// rsqrt(inv_d * sum(ssq[t][0..n_ssq)) + eps) (partials per 64 columns).
+struct PfHeadArgs {
+  const void* w;                      // BF16 [N][K]
+  int N, K;
   const uint16_t* x; int ldx; uint32_t plane;
   const float* ssq; int n_ssq; float inv_d, eps;
-  const float* resid;                 // MM_RESID: [T][ldy]
-  float* y; int ldy;                  // float32 output [T][ldy] (not MM_GATEUP)
-  uint16_t* xo; int ldxo; uint32_t plane_o;   // next operand (MM_GATEUP; MM_RESID with gamma_next)
-  const uint16_t* gamma_next;
-  float* ssq_out; int n_ssq_out;      // MM_RESID with gamma_next: [T][ceil(N/64)]
+  float* y; int ldy;
   int T;
-  float* part; size_t part_floats;    // MM_QKV / MM_RESID K-split partials [splits][T][N] (or null)
-  StoreView sv;                       // gs set: weights read from a groupwise store
 };
-hipError_t launch_pf_gemm(MfmaMode mode, const PfArgs& a, hipStream_t s);
+hipError_t launch_pf_head(const PfHeadArgs& a, hipStream_t s);
 // floats of the K-split partial buffer of a plan (prompt chunks up to max_prefill tokens, panels
 // of up to n_max rows)
 size_t pf_split_buffer_floats(int max_prefill, int n_max);
@@ -163,7 +156,7 @@ hipError_t launch_pf_prep(const float* x, int D, int T, const uint16_t* gamma, u
                           size_t plane, int ldxo, float* ssq, hipStream_t s);
 int pf_ssq_block();
 
-// Per-row INT8 panels on the INT8 matrix cores. The operand x holds one row of 4 ldx bytes per
+// Projections on the INT8 matrix cores. The operand x holds one row of 4 ldx bytes per
 // token: three planes of ldx signed base-256 digits (high to low), then the token's
 // float32 scale. MM_QKV: y = product; MM_RESID: y = resid + product; MM_GATEUP: y = silu(gate) *
 // up. With ks > 1 (not MM_GATEUP) split z writes its product to part [z][T][N] instead.
@@ -176,6 +169,10 @@ struct PfI8Args {
   float* y; int ldy;
   int T, ks;
   float* part; size_t part_floats;
+  // gs set: weights read from a groupwise store (w, w2_off, scale, ld unused). K is the operand's
+  // width, a multiple of 128: with a column map, 128 times the store chunks of 128 columns that
+  // hold any retained column, listed by launch_pf_quant in x
+  StoreView sv;
 };
 // the tile shape and the number of K splits for these sizes
 void plan_pf_i8(MfmaMode mode, const PfI8Args& a, int* shape, int* ks);
@@ -190,6 +187,7 @@ struct PfQuantArgs {
   const uint16_t* gamma; float inv_d, eps;
   const float* part; int ks; float* y;
   void* o; int ldo;
+  const int* cols; int store_cols;    // column map (StoreView::cols) and width of the store's rows
 };
 hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s);
 // y = resid + sum of part [ks][T][N], rows of N floats
@@ -216,8 +214,7 @@ struct PfAttnArgs {
   int slot_start[65];
   const uint16_t* kc; const uint16_t* vc;         // [Hkv][S][dh]
   int S, pos0, T;
-  float* o; int ldo;                              // [T][ldo], or the hi/lo operand [2][T][ldo]
-  uint16_t* o_hl; uint32_t o_plane;               // when o_hl is set
+  float* o; int ldo;                              // [T][ldo]
   // split query blocks: partial records (part_floats, nullable: no split) and one counter per
   // (retained head, query block), zero on entry and left zero
   float* part; size_t part_floats; int* cnt; int cnt_len;

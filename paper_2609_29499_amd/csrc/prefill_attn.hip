@@ -21,7 +21,7 @@
 //   * O += P V on v_mfma_f32_16x16x16_bf16 with P split into hi/lo BF16 and V units read from LDS;
 //     the output holds query 4 c + i in lane (r, c), so the per-query rescale factors move there
 //     by a lane permute.
-// The output O / l is written in float32, or as the hi/lo operand of the O projection.
+// The output O / l is written in float32.
 #include <algorithm>
 
 #include "device_common.hpp"
@@ -324,13 +324,7 @@ __global__ __launch_bounds__(kBlock) void pf_attn_kernel(PfAttnArgs a) {
     for (int d = 0; d < NDT; ++d) {
       const float v = o[d][i] * inv[i];
       const size_t at = size_t(t) * a.ldo + size_t(h) * DH + 16 * d + r;
-      if (!a.o_hl) {
-        a.o[at] = v;
-        continue;
-      }
-      const uint16_t hi = f32_to_bf16(v);
-      a.o_hl[at] = hi;
-      a.o_hl[a.o_plane + at] = f32_to_bf16(v - bf16_to_f32(hi));
+      a.o[at] = v;
     }
   }
 }

@@ -1,4 +1,4 @@
-// Prefill projections over per-row INT8 panels on the INT8 matrix cores:
+// Prefill projections over INT8 panels and over the groupwise store on the INT8 matrix cores:
 // C[t][n] = sum_k A[t][k] P[n][k] with v_mfma_i32_32x32x32_i8 and exact int32 accumulation.
 //
 // Operands. A token's activations are carried as 24-bit fixed point under one power-of-two scale
@@ -23,6 +23,15 @@
 // into two LDS stages (buffer loads with an LDS destination, 16-byte pieces XOR-swizzled by row on
 // the memory side), the next chunk in flight while one is multiplied, one barrier per chunk.
 //
+// Groupwise store (shared-store plans). A chunk of 128 columns is one scale group, so the three digit
+// sums of a chunk are exact integers that meet one BF16 scale: 256 d2 + d1 is formed in one int32
+// accumulator (shifted between the two passes), converted and added to a float32 sum with the
+// scale, then d0 (five vector operations per output and chunk next to 48 matrix operations per 64
+// outputs and lane). Rows come through the plan's row map; a column-mapped operand is laid out in
+// the store's own chunks, those with any retained column, dropped columns zero. It replaced four
+// passes of hi/lo weights times hi/lo activations on the BF16 matrix cores: one 8B layer at 1000
+// tokens 998 -> 548 us.
+//
 // What bounds it: power. At a full chip of 128 x 256 tiles the clock falls from 2.4 to 1.6-1.8 GHz
 // (cycle against real-time counters), a chunk of 64 takes about 2100 cycles of which 1536 are
 // matrix cycles, and the matrix cores alone on random registers reach 3.3 POP/s of the nominal 5.
@@ -41,6 +50,7 @@ namespace {
 
 typedef int __attribute__((ext_vector_type(4))) i32x4;
 typedef int __attribute__((ext_vector_type(16))) i32x16;
+typedef float __attribute__((ext_vector_type(16))) f32x16;
 // four floats of a caller's array, which is only 4-byte aligned
 typedef float __attribute__((ext_vector_type(4), aligned(4))) f32x4u;
 
@@ -82,15 +92,16 @@ __device__ __forceinline__ void tile_of(int id, int total, int gx, int gy, int& 
   bx = in / gm;
 }
 
-// MT x NT tiles of 32 tokens x 32 rows per wave; WGM x WGN waves; WAVES: per SIMD
-template <int MODE, int MT, int NT, int WGM, int WGN, int WAVES>
+// NT tiles of 32 tokens x 32 rows per wave; WGM x WGN waves; WAVES: per SIMD; SH: groupwise store
+template <int MODE, int NT, int WGM, int WGN, int WAVES, bool SH>
 __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a, int gx, int gy) {
   constexpr bool GU = (MODE == MM_GATEUP);
   constexpr int HN = 16 * NT;                           // gate/up: channels per wave
-  constexpr int TM = 32 * MT * WGM, TN = 32 * NT * WGN, NW = WGM * WGN;
-  constexpr int RPL = 1024 / kKC, LPR = kKC / 16;         // rows per 1 KiB load, lanes per row
+  constexpr int TM = 32 * WGM, TN = 32 * NT * WGN, NW = WGM * WGN;
+  constexpr int RPL = 1024 / kKC, LPR = kKC / 16;       // rows per 1 KiB load, lanes per row
   constexpr int APER = 3 * TM / RPL / NW, BPER = TN / RPL / NW;
   static_assert(APER * RPL * NW == 3 * TM && BPER * RPL * NW == TN, "even share of the loads");
+  static_assert(HN % (RPL * NW) == 0, "a panel load of a wave lies in gate or in up rows, the same for every wave");
   static_assert(TM <= 64 * NW, "one token scale per thread");
   __shared__ __attribute__((aligned(16))) I8Stage<TM, TN> st0;
   __shared__ __attribute__((aligned(16))) I8Stage<TM, TN> st1;
@@ -108,12 +119,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
 
   const uint32_t xrow = 4u * uint32_t(a.ldx);           // bytes of an operand row
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(a.x, uint32_t(T) * xrow);
-  const uint32_t ldw = uint32_t(a.ld);
-  const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.w, GU ? a.w2_off + uint32_t(N) * ldw : uint32_t(N) * ldw);
+  const uint32_t ldw = SH ? uint32_t(a.sv.ld) : uint32_t(a.ld);
+  const uint32_t w_bytes = (SH ? uint32_t(a.sv.store_rows) : uint32_t(N)) * ldw;
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(SH ? a.sv.w : a.w, !SH && GU ? a.w2_off + w_bytes : w_bytes);
+  const __amdgpu_buffer_rsrc_t rw2 = make_rsrc(SH && GU ? a.sv.w2 : nullptr, SH && GU ? w_bytes : 0u);
+  // store row of panel row `row` (-1 past the panel)
+  auto panel_row = [&](int row) { return row >= N ? -1 : (SH && a.sv.rows ? a.sv.rows[row] : row); };
 
   // this lane's share of a chunk: a load covers RPL rows, LPR lanes each; the wave's loads are
   // digit rows RPL (wave + NW j) .. (plane-major), then panel rows RPL (wave + NW j) ..
   uint32_t abase[APER], bbase[BPER];
+  // panel load j: gate or up rows
+  auto up_load = [](int j) { return GU && (RPL * NW * j) % (2 * HN) >= HN; };
 #pragma unroll
   for (int j = 0; j < APER; ++j) {
     const int i = wave + NW * j, plane = i / (TM / RPL);
@@ -123,21 +140,64 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
 #pragma unroll
   for (int j = 0; j < BPER; ++j) {
     const int lr = (wave + NW * j) * RPL + lane / LPR;
-    const int row = GU ? n0 + HN * (lr / (2 * HN)) + lr % HN : n0 + lr;
-    const bool up = GU && lr % (2 * HN) >= HN;
-    bbase[j] = row < N ? (up ? a.w2_off : 0u) + uint32_t(row) * ldw + 16u * slot(lr, lane % LPR) : kOOB;
+    const int row = panel_row(GU ? n0 + HN * (lr / (2 * HN)) + lr % HN : n0 + lr);
+    bbase[j] = row >= 0 ? (!SH && up_load(j) ? a.w2_off : 0u) + uint32_t(row) * ldw + 16u * slot(lr, lane % LPR) : kOOB;
   }
-  // chunks past the last reload it (into a stage that is not read again), so that every step
-  // issues alike. A panel row may end inside its last chunk: the bytes loaded past it are the next
-  // row's, or of the sections behind the panels, and meet zero digits.
-  auto issue = [&](int kc, I8Stage<TM, TN>& S) {
-    const int k0 = (kc0 + max(min(kc, nk - 1), 0)) * kKC;
+  // Chunks past the last reload it (into a stage that is not read again), so that every step
+  // issues alike. A row of a per-row panel may end inside its last chunk: the bytes loaded past it
+  // are the next row's, or of the sections behind the panels, and meet zero digits. Store rows are
+  // whole chunks; with a column map the operand's chunk kc is the kc-th store chunk with any
+  // retained column, listed behind the first token's scale.
+  const bool mapped = SH && a.sv.cols != nullptr;
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.x + 3 * size_t(a.ldx) + 16, mapped ? uint32_t(nk_all) * 4u : 0u);
+  auto clamp_chunk = [&](int kc) { return kc0 + max(min(kc, nk - 1), 0); };
+  auto list_entry = [&](int kc) {                       // loaded one step before it is used
+    return mapped ? __builtin_amdgcn_raw_buffer_load_b32(rl, 4 * clamp_chunk(kc), 0, 0) : 0u;
+  };
+  auto store_chunk = [&](int kc, uint32_t entry) {
+    return mapped ? int(__builtin_amdgcn_readfirstlane(int(entry))) : clamp_chunk(kc);
+  };
+  auto issue = [&](int kc, int wc, I8Stage<TM, TN>& S) {
+    const int k0 = clamp_chunk(kc) * kKC, kw = SH ? wc * kKC : k0;
 #pragma unroll
     for (int j = 0; j < APER; ++j)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S.a[(wave + NW * j) * 1024]), 16, int(abase[j]), k0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < BPER; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, static_cast<void*>(&S.b[(wave + NW * j) * 1024]), 16, int(bbase[j]), k0, 0, 0);
+    for (int j = 0; j < BPER; ++j) {
+      const __amdgpu_buffer_rsrc_t rj = SH && up_load(j) ? rw2 : rw;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rj, static_cast<void*>(&S.b[(wave + NW * j) * 1024]), 16, int(bbase[j]), kw, 0, 0);
+    }
+  };
+
+  // panel rows of the lane's outputs, and (groupwise store) the byte offsets of their scales
+  int col[NT];
+  uint32_t gbase[SH ? NT : 1];
+  const uint32_t sgroups = ldw / 128u;
+  const __amdgpu_buffer_rsrc_t rg = make_rsrc(SH ? a.sv.gs : nullptr, SH ? uint32_t(a.sv.store_rows) * sgroups * 2u : 0u);
+  const __amdgpu_buffer_rsrc_t rg2 = make_rsrc(SH && GU ? a.sv.gs2 : nullptr,
+                                               SH && GU ? uint32_t(a.sv.store_rows) * sgroups * 2u : 0u);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    col[nt] = GU ? n0 + HN * wn + 32 * (nt % (NT / 2)) + r : n0 + (wn * NT + nt) * 32 + r;
+    if constexpr (SH) {
+      const int row = panel_row(col[nt]);
+      gbase[nt] = row >= 0 ? uint32_t(row) * sgroups * 2u : kOOB;
+    }
+  }
+  struct Scales {
+    uint32_t s[SH ? NT : 1];
+  };
+  auto load_scales = [&](int wc) {
+    Scales v{};
+    if constexpr (SH) {
+      const int off = 2 * wc;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const __amdgpu_buffer_rsrc_t rn = GU && nt >= NT / 2 ? rg2 : rg;
+        v.s[nt] = __builtin_amdgcn_raw_buffer_load_b16(rn, int(gbase[nt]), off, 0);
+      }
+    }
+    return v;
   };
 
   // the token scales go first, so that waiting for them does not wait for the chunks
@@ -146,49 +206,97 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
     const uint32_t off = uint32_t(m0 + tid) * xrow + 3u * uint32_t(a.ldx);
     tscale = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, int(m0 + tid < T ? off : kOOB), 0, 0));
   }
-  issue(0, st0);
+  const int first = store_chunk(0, list_entry(0));
+  uint32_t entry = list_entry(1);
+  Scales sc0 = load_scales(first), sc1{};
+  issue(0, first, st0);
 
-  i32x16 acc[3][MT][NT];
+  // per-row panels: the digit sums over all of K; groupwise store: the scaled float32 sum, and the
+  // digit sums of one chunk (one scale group) at a time
+  i32x16 acc[SH ? 1 : 3][SH ? 1 : NT];
+  f32x16 facc[SH ? NT : 1];
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int d = 0; d < (SH ? 1 : 3); ++d)
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int j = 0; j < (SH ? 1 : NT); ++j)
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
+      for (int e = 0; e < 16; ++e) acc[d][j][e] = 0;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[d][i][j][e] = 0;
+  for (int j = 0; j < (SH ? NT : 1); ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) facc[j][e] = 0.0f;
 
-  auto compute = [&](const I8Stage<TM, TN>& S) {
+  auto frag_a = [&](const I8Stage<TM, TN>& S, int d, int ks) {   // (tile rows differ from r by multiples of 32)
+    return *reinterpret_cast<const i32x4*>(&S.a[d * TM * kKC + (wm * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
+  };
+  auto frag_b = [&](const I8Stage<TM, TN>& S, int nt, int ks) {
+    return *reinterpret_cast<const i32x4*>(&S.b[((wn * NT + nt) * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
+  };
+  auto compute = [&](const I8Stage<TM, TN>& S, const Scales& sv) {
+    if constexpr (!SH) {
 #pragma unroll 2
-    for (int ks = 0; ks < kKC / 32; ++ks) {
-      const int sl = 16 * slot(r, 2 * ks + hi);         // (rows differ from r by multiples of 32)
-      i32x4 bf[NT];
+      for (int ks = 0; ks < kKC / 32; ++ks) {
+        i32x4 bf[NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        bf[nt] = *reinterpret_cast<const i32x4*>(&S.b[((wn * NT + nt) * 32 + r) * kKC + sl]);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+        for (int nt = 0; nt < NT; ++nt) bf[nt] = frag_b(S, nt, ks);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          const i32x4 af = *reinterpret_cast<const i32x4*>(&S.a[d * TM * kKC + ((wm * MT + mt) * 32 + r) * kKC + sl]);
+          const i32x4 af = frag_a(S, d, ks);
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt)
-            acc[d][mt][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, bf[nt], acc[d][mt][nt], 0, 0, 0);
+            acc[d][nt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, bf[nt], acc[d][nt], 0, 0, 0);
         }
+      }
+    } else {
+      // |256 d2 + d1 sums| <= 128 * 127 * 32768 < 2^29.0 and |d0 sum| <= 2^21: both exact in int32
+      // two row tiles at a time, so that their fragments and sums fit the registers
+#pragma unroll
+      for (int h = 0; h < NT; h += 2) {
+        __builtin_amdgcn_sched_barrier(0);              // (overlapping the pairs spills)
+        i32x4 bf[kKC / 32][2];
+#pragma unroll
+        for (int ks = 0; ks < kKC / 32; ++ks)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) bf[ks][j] = frag_b(S, h + j, ks);
+        i32x16 u[2];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) u[j][e] = d == 1 ? u[j][e] << 8 : 0;
+#pragma unroll
+          for (int ks = 0; ks < kKC / 32; ++ks) {
+            const i32x4 af = frag_a(S, d, ks);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) u[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af, bf[ks][j], u[j], 0, 0, 0);
+          }
+          if (d == 0) continue;
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const float s = bf16_to_f32(uint16_t(sv.s[h + j])) * (d == 1 ? 256.0f : 1.0f);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) facc[h + j][e] = fmaf(float(u[j][e]), s, facc[h + j][e]);
+          }
+        }
+      }
     }
   };
   // chunk kc sits in stage kc % 2: wait for this wave's loads of it, meet the other waves (their
   // loads of it have landed, and all of them are done with the other stage), load the next chunk
   // into the other stage, multiply
-  auto step = [&](int kc, const I8Stage<TM, TN>& cur, I8Stage<TM, TN>& nxt) {
+  auto step = [&](int kc, const I8Stage<TM, TN>& cur, I8Stage<TM, TN>& nxt, const Scales& sv, Scales& sn) {
     wait_vm0();
     __builtin_amdgcn_s_barrier();
-    issue(kc + 1, nxt);
-    compute(cur);
+    const int wc = store_chunk(kc + 1, entry);
+    entry = list_entry(kc + 2);
+    if constexpr (SH) sn = load_scales(wc);
+    issue(kc + 1, wc, nxt);
+    compute(cur, sv);
   };
   for (int kc = 0; kc < nk; kc += 2) {
-    step(kc, st0, st1);
-    if (kc + 1 < nk) step(kc + 1, st1, st0);
+    step(kc, st0, st1, sc0, sc1);
+    if (kc + 1 < nk) step(kc + 1, st1, st0, sc1, sc0);
   }
   wait_vm0();
   __syncthreads();                                      // every wave is done with the stages
@@ -196,42 +304,43 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
   if (tid < TM) ts[tid] = tscale;
   __syncthreads();
 
-  // ---- epilogue: lane (r, hi) holds tokens 8 g + 4 hi + i of each token tile for row r
+  // ---- epilogue: lane (r, hi) holds tokens 8 g + 4 hi + i of the token tile for row r
   float sc[NT];
-  int col[NT];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    col[nt] = GU ? n0 + HN * wn + 32 * (nt % (NT / 2)) + r : n0 + (wn * NT + nt) * 32 + r;
-    sc[nt] = col[nt] < N ? (GU && nt >= NT / 2 ? a.scale2 : a.scale)[col[nt]] : 0.0f;
-  }
-  float* part = a.ks > 1 ? a.part + size_t(bz) * T * N : nullptr;
+  for (int nt = 0; nt < NT; ++nt)
+    sc[nt] = SH ? 1.0f : (col[nt] < N ? (GU && nt >= NT / 2 ? a.scale2 : a.scale)[col[nt]] : 0.0f);
+  // the outputs through buffers (offsets past the end read zero and store nothing), the residuals
+  // of a row tile loaded together
+  const bool split = a.ks > 1;
+  const uint32_t ldo = split ? uint32_t(N) : uint32_t(a.ldy);
+  float* const dst = split ? a.part + size_t(bz) * T * N : a.y;
+  const __amdgpu_buffer_rsrc_t ry = make_rsrc(dst, (uint32_t(T - 1) * ldo + uint32_t(N)) * 4u);
+  const bool resid = MODE == MM_RESID && !split;
+  const __amdgpu_buffer_rsrc_t rr = make_rsrc(resid ? a.resid : nullptr, resid ? (uint32_t(T - 1) * ldo + uint32_t(N)) * 4u : 0u);
+  auto value = [&](int nt, int e, float tsc) {
+    if constexpr (SH) return facc[nt][e] * tsc;
+    else return join(acc[0][nt][e], acc[1][nt][e], acc[2][nt][e]) * tsc * sc[nt];
+  };
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int nt = 0; nt < (GU ? NT / 2 : NT); ++nt) {
+    uint32_t off[16];
+    float tsc[16], res[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int tl = (wm * MT + mt) * 32 + 8 * (e >> 2) + 4 * hi + (e & 3);
-      const int t = m0 + tl;
-      if (t >= T) continue;
-      const float tsc = ts[tl];
-      float v[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        v[nt] = join(acc[0][mt][nt][e], acc[1][mt][nt][e], acc[2][mt][nt][e]) * tsc * sc[nt];
-      if constexpr (GU) {
-#pragma unroll
-        for (int nt = 0; nt < NT / 2; ++nt)
-          if (col[nt] < N)
-            a.y[size_t(t) * a.ldy + col[nt]] = v[nt] / (1.0f + exp2f(-v[nt] * kLog2e)) * v[nt + NT / 2];
-      } else {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          if (col[nt] >= N) continue;
-          if (part) part[size_t(t) * N + col[nt]] = v[nt];
-          else if (MODE == MM_RESID) a.y[size_t(t) * a.ldy + col[nt]] = a.resid[size_t(t) * a.ldy + col[nt]] + v[nt];
-          else a.y[size_t(t) * a.ldy + col[nt]] = v[nt];
-        }
-      }
+      const int tl = wm * 32 + 8 * (e >> 2) + 4 * hi + (e & 3), t = m0 + tl;
+      tsc[e] = ts[tl];
+      off[e] = t < T && col[nt] < N ? (uint32_t(t) * ldo + uint32_t(col[nt])) * 4u : kOOB;
+      if constexpr (MODE == MM_RESID)
+        res[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, int(off[e]), 0, 0));
     }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      float v = value(nt, e, tsc[e]);
+      if constexpr (GU) v = v / (1.0f + exp2f(-v * kLog2e)) * value(nt + NT / 2, e, tsc[e]);
+      else if constexpr (MODE == MM_RESID) v += res[e];
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), ry, int(off[e]), 0, 0);
+    }
+  }
 }
 
 // Float32 rows -> digit rows. One workgroup per token; thread i holds elements 4 (i + THREADS j).
@@ -240,20 +349,58 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
 // row is read in full before any digit is written, so source and destination may be one buffer.
 // The scale is the largest power of two 2^-e that keeps q = rint(v 2^e) within three digits
 // (|q| <= 0x7f7f7f); a row with a non-finite value gets a NaN scale, a zero row digits of zero.
+// MAPPED (groupwise store, no gain, no splits): x holds the retained columns in pieces of 16, piece p
+// being store columns cols[p] .. + 15; the operand holds the store's chunks of 128 columns with any
+// retained piece, in order, dropped pieces zero, and their list is written behind token 0's scale.
 // Bound by its 4 to 8 bytes read and 3 written per element.
-template <int THREADS, int NV>
+constexpr int kMaxPieces = 2560;        // store pieces of the widest input (40960 columns)
+template <int THREADS, int NV, bool MAPPED>
 __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
   __shared__ float red[2][THREADS / kWave];
   const int tid = threadIdx.x, t = blockIdx.x, K = a.K, ld = a.ldo;
-  const int kz = (K + kKC - 1) / kKC * kKC;              // digits written: K and its zero padding
+  int kz = (K + kKC - 1) / kKC * kKC;                    // digits written: K and its zero padding
+  uint8_t* row = reinterpret_cast<uint8_t*>(a.o) + size_t(t) * 4 * ld;
+  __shared__ short inv[MAPPED ? kMaxPieces : 1];         // store piece -> plan piece, -1 dropped
+  __shared__ short chunk[MAPPED ? kMaxPieces / 8 : 1];   // operand chunk -> store chunk
+  if constexpr (MAPPED) {
+    const int np = a.store_cols / 16, nc = a.store_cols / kKC;
+    __shared__ int n_chunks;
+    for (int i = tid; i < np; i += THREADS) inv[i] = -1;
+    __syncthreads();
+    for (int p = tid; p < K / 16; p += THREADS) inv[a.cols[p] >> 4] = short(p);
+    __syncthreads();
+    if (tid < kWave) {
+      int n = 0;
+      for (int c0 = 0; c0 < nc; c0 += kWave) {
+        const int c = c0 + tid;
+        bool any = false;
+        if (c < nc)
+          for (int i = 0; i < 8; ++i) any |= inv[8 * c + i] >= 0;
+        const unsigned long long m = __ballot(any);
+        if (any) chunk[n + __popcll(m & ((1ull << tid) - 1))] = short(c);
+        n += __popcll(m);
+      }
+      if (tid == 0) n_chunks = n;
+    }
+    __syncthreads();
+    kz = n_chunks * kKC;
+  }
   float4 v[NV];
   float amax = 0.0f, ss = 0.0f;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int k = 4 * (tid + THREADS * j);
     v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (k >= K) continue;                               // (K % 4 == 0 or the rest of the row is padding)
-    const f32x4u xv = *reinterpret_cast<const f32x4u*>(a.x + size_t(t) * a.ldx + k);
+    int src = k;
+    if constexpr (MAPPED) {
+      if (k >= kz) continue;
+      const int p = inv[8 * chunk[k / kKC] + (k % kKC) / 16];
+      if (p < 0) continue;
+      src = 16 * p + k % 16;
+    } else if (k >= K) {
+      continue;                                         // (K % 4 == 0 or the rest of the row is padding)
+    }
+    const f32x4u xv = *reinterpret_cast<const f32x4u*>(a.x + size_t(t) * a.ldx + src);
     v[j] = make_float4(xv.x, xv.y, xv.z, xv.w);
     for (int z = 0; z < a.ks; ++z) {
       const float4 p = *reinterpret_cast<const float4*>(a.part + (size_t(z) * a.T + t) * K + k);
@@ -264,7 +411,7 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
       ss = fmaf(v[j].x, v[j].x, fmaf(v[j].y, v[j].y, fmaf(v[j].z, v[j].z, fmaf(v[j].w, v[j].w, ss))));
       const uint2 g = *reinterpret_cast<const uint2*>(a.gamma + k);
       v[j].x *= bf16_lo(g.x); v[j].y *= bf16_hi(g.x); v[j].z *= bf16_lo(g.y); v[j].w *= bf16_hi(g.y);
-    } else {
+    } else if (!MAPPED) {
       // columns past K of the last four are padding, whatever the buffer holds
       if (k + 1 >= K) v[j].y = 0.0f;
       if (k + 2 >= K) v[j].z = 0.0f;
@@ -303,7 +450,6 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
   if (mb < 0x00800000u || e > 126) e = 126;
   if (ldexpf(big, e) > 8355711.0f) --e;
   const float up = ldexpf(1.0f, e > 127 ? 127 : e);
-  uint8_t* row = reinterpret_cast<uint8_t*>(a.o) + size_t(t) * 4 * ld;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int k = 4 * (tid + THREADS * j);
@@ -327,6 +473,10 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
     float s = ldexpf(1.0f, -e);
     if (a.gamma) s *= rsqrtf(ss * a.inv_d + a.eps);
     *reinterpret_cast<float*>(row + 3 * size_t(ld)) = finite ? s : __uint_as_float(0x7fc00000u);
+  }
+  if constexpr (MAPPED) {
+    if (t == 0)
+      for (int i = tid; i < kz / kKC; i += THREADS) reinterpret_cast<int*>(row + 3 * size_t(ld) + 16)[i] = chunk[i];
   }
 }
 
@@ -368,27 +518,27 @@ float launch_us(const Shape& h, long w, int n) {
   return kFixedUs + float(n) * (float(rounds) * h.t_full + (rest ? chunk(rest) : 0.0f));
 }
 
-template <int MODE>
+template <int MODE, bool SH>
 hipError_t launch_mode(const PfI8Args& a, int shape, hipStream_t s) {
   const Shape& h = kShapes[shape];
   const int rows = MODE == MM_GATEUP ? h.tn / 2 : h.tn;
   const int gx = (a.N + rows - 1) / rows, gy = (a.T + h.tm - 1) / h.tm;
   const dim3 grid(uint32_t(gx) * uint32_t(gy) * uint32_t(a.ks));
-  if (shape == 0) hipLaunchKernelGGL((pf_i8_kernel<MODE, 1, 4, 4, 2, 2>), grid, dim3(512), 0, s, a, gx, gy);
-  else if (shape == 1) hipLaunchKernelGGL((pf_i8_kernel<MODE, 1, 2, 2, 2, 2>), grid, dim3(256), 0, s, a, gx, gy);
-  else hipLaunchKernelGGL((pf_i8_kernel<MODE, 1, 2, 1, 2, 1>), grid, dim3(128), 0, s, a, gx, gy);
+  if (shape == 0) hipLaunchKernelGGL((pf_i8_kernel<MODE, 4, 4, 2, 2, SH>), grid, dim3(512), 0, s, a, gx, gy);
+  else if (shape == 1) hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 2, 2, 2, SH>), grid, dim3(256), 0, s, a, gx, gy);
+  else hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 1, 2, 1, SH>), grid, dim3(128), 0, s, a, gx, gy);
   return hipGetLastError();
 }
 
-template <int THREADS>
-hipError_t launch_quant(const PfQuantArgs& a, hipStream_t s) {
-  const int nv = ((a.K + kKC - 1) / kKC * kKC + 4 * THREADS - 1) / (4 * THREADS);
+template <int THREADS, bool MAPPED>
+hipError_t launch_quant(const PfQuantArgs& a, int width, hipStream_t s) {
+  const int nv = ((width + kKC - 1) / kKC * kKC + 4 * THREADS - 1) / (4 * THREADS);
   const dim3 g(a.T), b(THREADS);
-  if (nv <= 1) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 1>), g, b, 0, s, a);
-  else if (nv <= 2) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 2>), g, b, 0, s, a);
-  else if (nv <= 4) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 4>), g, b, 0, s, a);
-  else if (nv <= 7) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 7>), g, b, 0, s, a);
-  else if (nv <= 11) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 11>), g, b, 0, s, a);
+  if (nv <= 1) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 1, MAPPED>), g, b, 0, s, a);
+  else if (nv <= 2) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 2, MAPPED>), g, b, 0, s, a);
+  else if (nv <= 4) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 4, MAPPED>), g, b, 0, s, a);
+  else if (nv <= 7) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 7, MAPPED>), g, b, 0, s, a);
+  else if (nv <= 11) hipLaunchKernelGGL((pf_quant_kernel<THREADS, 11, MAPPED>), g, b, 0, s, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -425,15 +575,25 @@ void plan_pf_i8(MfmaMode mode, const PfI8Args& a, int* shape, int* ks) {
 }
 
 hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t s) {
-  if (a.T < 1 || a.K < 0 || a.K > a.ld || a.ld % 16 != 0 || a.ldx % kKC != 0 || a.ldx < a.K || a.ks < 1 ||
+  if (a.sv.gs) {
+    // store rows in whole chunks, one scale group each
+    if (a.K % kKC != 0 || a.sv.ld % kKC != 0 || a.K > a.sv.ld || a.sv.store_rows < 1 ||
+        (mode == MM_GATEUP && (!a.sv.w2 || !a.sv.gs2)))
+      return hipErrorInvalidValue;
+  } else if (a.K > a.ld || a.ld % 16 != 0) {
+    return hipErrorInvalidValue;
+  }
+  if (a.T < 1 || a.K < 0 || a.ldx % kKC != 0 || a.ldx < a.K || a.ks < 1 ||
       shape < 0 || shape > 2 || size_t(a.T) * 4 * a.ldx >= size_t(kOOB) ||
+      size_t(a.T) * 4 * std::max(a.ldy, a.N) >= size_t(kOOB) ||
       (a.ks > 1 && (mode == MM_GATEUP || !a.part || size_t(a.ks) * a.T * a.N > a.part_floats)))
     return hipErrorInvalidValue;
   if (a.N == 0) return hipSuccess;
+  const bool sh = a.sv.gs != nullptr;
   switch (mode) {
-    case MM_QKV: return launch_mode<MM_QKV>(a, shape, s);
-    case MM_RESID: return launch_mode<MM_RESID>(a, shape, s);
-    case MM_GATEUP: return launch_mode<MM_GATEUP>(a, shape, s);
+    case MM_QKV: return sh ? launch_mode<MM_QKV, true>(a, shape, s) : launch_mode<MM_QKV, false>(a, shape, s);
+    case MM_RESID: return sh ? launch_mode<MM_RESID, true>(a, shape, s) : launch_mode<MM_RESID, false>(a, shape, s);
+    case MM_GATEUP: return sh ? launch_mode<MM_GATEUP, true>(a, shape, s) : launch_mode<MM_GATEUP, false>(a, shape, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -441,7 +601,15 @@ hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t
 hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s) {
   if (a.T < 1 || a.K < 0 || a.ldo % kKC != 0 || a.ldo < a.K || a.ldx % 4 != 0 || ((a.gamma || a.ks) && a.K % 4 != 0))
     return hipErrorInvalidValue;
-  return a.K <= 4 * 256 * 7 ? launch_quant<256>(a, s) : launch_quant<1024>(a, s);
+  if (a.cols) {
+    // the operand's width is at most the store's (one register array holds the row)
+    if (a.gamma || a.ks || a.K % 16 != 0 || a.store_cols % kKC != 0 || a.store_cols < a.K ||
+        a.store_cols > 16 * kMaxPieces || a.ldo < a.store_cols)
+      return hipErrorInvalidValue;
+    return a.store_cols <= 4 * 256 * 7 ? launch_quant<256, true>(a, a.store_cols, s)
+                                       : launch_quant<1024, true>(a, a.store_cols, s);
+  }
+  return a.K <= 4 * 256 * 7 ? launch_quant<256, false>(a, a.K, s) : launch_quant<1024, false>(a, a.K, s);
 }
 
 hipError_t launch_pf_i8_reduce(const float* part, int ks, const float* resid, float* y, int T, int N,

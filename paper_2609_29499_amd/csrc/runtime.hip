@@ -315,6 +315,8 @@ double layer_flops(const tasp_model_desc* d, int m_q, int m_kv, int c) {
 
 struct LayerPlan {
   int m_q, m_kv, c, n_qkv, ld_o, ld_d;
+  int o_chunks, d_chunks;            // shared-store plans: chunks of 128 store columns with any
+                                     // retained column, of W_o and W_down
   int8_t *qkv, *o, *g, *u, *dn;
   float *s_qkv, *s_o, *s_g, *s_u, *s_d;
   uint16_t *an, *fn;
@@ -654,18 +656,6 @@ tasp_status decode_batched(tasp_plan p, const float* x, tasp_kv_cache* cache, in
 
 // ---- prefill (T tokens of one sequence): projections and attention on the matrix cores
 
-tasp::PfArgs pf_base(const tasp_plan_s* p, int T) {
-  tasp::PfArgs a{};
-  a.T = T;
-  a.inv_d = 1.0f / float(p->desc.d_model);
-  a.eps = p->desc.rms_eps;
-  a.n_ssq = (p->desc.d_model + tasp::pf_ssq_block() - 1) / tasp::pf_ssq_block();
-  a.n_ssq_out = a.n_ssq;
-  a.part = p->ppart;
-  a.part_floats = p->ppart_floats;
-  return a;
-}
-
 // final norm + LM head of a prefill whose last residual is r: every token's logits, or (last_only)
 // the last token's by the decode LM head GEMV over that token's row (greedy decoding needs no
 // other)
@@ -681,18 +671,22 @@ tasp_status prefill_head(tasp_plan p, const float* r, int T, float* out, hipStre
     a.B = 1;
     return run_kernel(tm, 5, s, [&] { return tasp::launch_gemv(tasp::GEMV_LMHEAD, a, s); });
   }
-  tasp::PfArgs a = pf_base(p, T);
-  const uint32_t plane_d = uint32_t(size_t(d.max_prefill) * p->ld_xd);
-  a.w = p->lm_head; a.N = d.vocab; a.K = D; a.ld = D; a.x = p->pxd; a.ldx = p->ld_xd;
-  a.plane = plane_d; a.ssq = p->pssq; a.y = out; a.ldy = d.vocab;
-  return run_kernel(tm, 5, s, [&] { return tasp::launch_pf_gemm(tasp::MM_LMHEAD, a, s); });
+  const uint32_t plane = uint32_t(size_t(d.max_prefill) * p->ld_xd);
+  tasp_status st = run_kernel(tm, 6, s, [&] {
+    return tasp::launch_pf_prep(r, D, T, p->final_norm, p->pxd, plane, p->ld_xd, p->pssq, s);
+  });
+  if (st) return st;
+  tasp::PfHeadArgs a{};
+  a.w = p->lm_head; a.N = d.vocab; a.K = D; a.x = p->pxd; a.ldx = p->ld_xd; a.plane = plane; a.T = T;
+  a.ssq = p->pssq; a.n_ssq = (D + tasp::pf_ssq_block() - 1) / tasp::pf_ssq_block();
+  a.inv_d = 1.0f / float(D); a.eps = d.rms_eps; a.y = out; a.ldy = d.vocab;
+  return run_kernel(tm, 5, s, [&] { return tasp::launch_pf_head(a, s); });
 }
 
-// prefill of a per-row plan: every projection on the INT8 matrix cores over digit operands. The
-// normed inputs (QKV, gate/up) have their digits in pxd; the O and down inputs are written to pxw
+// every projection on the INT8 matrix cores over digit operands. The normed inputs (QKV, gate/up) have their digits in pxd; the O and down inputs are written to pxw
 // in float32 and turned into digits there.
-tasp_status prefill_i8(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0, float* out,
-                       hipStream_t s, Timer* tm, bool last_only) {
+tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0, float* out,
+                         hipStream_t s, Timer* tm, bool last_only) {
   const tasp_model_desc& d = p->desc;
   const int D = d.d_model, dh = d.head_dim, L = d.n_layers, Pm = d.max_prefill;
   const uint32_t plane_q = uint32_t(size_t(d.n_q_heads) * Pm * dh);
@@ -712,9 +706,11 @@ tasp_status prefill_i8(tasp_plan p, const float* x, int T, tasp_kv_cache* cache,
     a.part = p->ppart; a.ks = ks > 1 ? ks : 0; a.y = y; a.o = p->pxd; a.ldo = p->ld_xd;
     return run_kernel(tm, 6, s, [&] { return tasp::launch_pf_quant(a, s); });
   };
-  auto quant_wide = [&](int K) {
+  // a shared-store plan's columns go to their places in the store's chunks (cols)
+  auto quant_wide = [&](int K, const tasp::StoreView& v) {
     tasp::PfQuantArgs a{};
     a.x = wide; a.ldx = p->ld_xw; a.K = K; a.T = T; a.o = wide; a.ldo = p->ld_xw;
+    a.cols = v.cols; a.store_cols = v.ld;
     return run_kernel(tm, 6, s, [&] { return tasp::launch_pf_quant(a, s); });
   };
   if ((st = quant_norm(x, p->layers[0].an, 1, nullptr))) return st;
@@ -728,6 +724,7 @@ tasp_status prefill_i8(tasp_plan p, const float* x, int T, tasp_kv_cache* cache,
       tasp::PfI8Args a{};
       a.w = P.qkv; a.scale = P.s_qkv; a.N = P.n_qkv; a.K = D; a.ld = D;
       a.x = reinterpret_cast<uint8_t*>(p->pxd); a.ldx = p->ld_xd; a.y = p->pqkv; a.ldy = p->ld_qkv;
+      if (p->shared) a.sv = store_view(p, l, 0);
       if ((st = gemm(0, tasp::MM_QKV, a))) return st;
       tasp::PfRopeArgs r{};
       r.qkv = p->pqkv; r.ld_qkv = p->ld_qkv; r.ks = a.ks;
@@ -748,26 +745,34 @@ tasp_status prefill_i8(tasp_plan p, const float* x, int T, tasp_kv_cache* cache,
       t.part = p->ppart; t.part_floats = p->ppart_floats; t.cnt = p->pacnt; t.cnt_len = p->pacnt_len;
       if ((st = run_kernel(tm, 1, s, [&] { return tasp::launch_pf_attn(t, s); }))) return st;
     }
-    if ((st = quant_wide(P.m_q * dh))) return st;
+    const tasp::StoreView vo = p->shared ? store_view(p, l, 1) : tasp::StoreView{};
+    const tasp::StoreView vd = p->shared ? store_view(p, l, 4) : tasp::StoreView{};
+    if ((st = quant_wide(P.m_q * dh, vo))) return st;
     {
       tasp::PfI8Args a{};
-      a.w = P.o; a.scale = P.s_o; a.N = D; a.K = P.m_q * dh; a.ld = P.ld_o;
+      a.w = P.o; a.scale = P.s_o; a.N = D; a.K = p->shared ? 128 * P.o_chunks : P.m_q * dh; a.ld = P.ld_o;
+      a.sv = vo;
       a.x = reinterpret_cast<uint8_t*>(p->pxw); a.ldx = p->ld_xw; a.resid = in; a.y = p->pr_mid; a.ldy = D;
       if ((st = gemm(2, tasp::MM_RESID, a))) return st;
       if ((st = quant_norm(a.ks > 1 ? in : p->pr_mid, P.fn, a.ks, p->pr_mid))) return st;
     }
     if (P.c > 0) {
       tasp::PfI8Args a{};
-      a.w = P.g;
-      a.w2_off = uint32_t(reinterpret_cast<const char*>(P.u) - reinterpret_cast<const char*>(P.g));
+      if (p->shared) {
+        a.sv = store_view(p, l, 3);
+      } else {
+        a.w = P.g;
+        a.w2_off = uint32_t(reinterpret_cast<const char*>(P.u) - reinterpret_cast<const char*>(P.g));
+      }
       a.scale = P.s_g; a.scale2 = P.s_u; a.N = P.c; a.K = D; a.ld = D;
       a.x = reinterpret_cast<uint8_t*>(p->pxd); a.ldx = p->ld_xd; a.y = wide; a.ldy = p->ld_xw;
       if ((st = gemm(3, tasp::MM_GATEUP, a))) return st;
     }
-    if ((st = quant_wide(P.c))) return st;
+    if ((st = quant_wide(P.c, vd))) return st;
     {
       tasp::PfI8Args a{};
-      a.w = P.dn; a.scale = P.s_d; a.N = D; a.K = P.c; a.ld = P.ld_d;
+      a.w = P.dn; a.scale = P.s_d; a.N = D; a.K = p->shared ? 128 * P.d_chunks : P.c; a.ld = P.ld_d;
+      a.sv = vd;
       a.x = reinterpret_cast<uint8_t*>(p->pxw); a.ldx = p->ld_xw; a.resid = p->pr_mid; a.y = lo; a.ldy = D;
       if ((st = gemm(4, tasp::MM_RESID, a))) return st;
       if (l + 1 < L) {
@@ -778,96 +783,6 @@ tasp_status prefill_i8(tasp_plan p, const float* x, int T, tasp_kv_cache* cache,
              })))
           return st;
       }
-    }
-  }
-  if (!d.vocab) return TASP_OK;
-  const float* r = p->pr_io[(L - 1) & 1];
-  if (!last_only &&
-      (st = run_kernel(tm, 6, s, [&] {
-         return tasp::launch_pf_prep(r, D, T, p->final_norm, p->pxd, uint32_t(size_t(Pm) * p->ld_xd), p->ld_xd,
-                                     p->pssq, s);
-       })))
-    return st;
-  return prefill_head(p, r, T, out, s, tm, last_only);
-}
-
-tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0,
-                         float* out, hipStream_t s, Timer* tm, bool last_only) {
-  if (!p->shared) return prefill_i8(p, x, T, cache, pos0, out, s, tm, last_only);
-  const tasp_model_desc& d = p->desc;
-  const int D = d.d_model, dh = d.head_dim, L = d.n_layers, Pm = d.max_prefill;
-  const uint32_t plane_d = uint32_t(size_t(Pm) * p->ld_xd);
-  const uint32_t plane_w = uint32_t(size_t(Pm) * p->ld_xw);
-  const uint32_t plane_q = uint32_t(size_t(d.n_q_heads) * Pm * dh);
-  const size_t layer_cache = size_t(cache->batch) * d.n_kv_heads * cache->max_seq * dh;
-  tasp_status st;
-  if ((st = run_kernel(tm, 6, s, [&] {
-         return tasp::launch_pf_prep(x, D, T, p->layers[0].an, p->pxd, plane_d, p->ld_xd, p->pssq, s);
-       })))
-    return st;
-  for (int l = 0; l < L; ++l) {
-    const LayerPlan& P = p->layers[l];
-    const float* in = (l == 0) ? x : p->pr_io[(l - 1) & 1];
-    float* lo = (l == L - 1 && d.vocab == 0) ? out : p->pr_io[l & 1];
-    uint16_t* kc = static_cast<uint16_t*>(cache->k) + l * layer_cache;
-    uint16_t* vc = static_cast<uint16_t*>(cache->v) + l * layer_cache;
-    if (P.n_qkv > 0) {
-      tasp::PfArgs a = pf_base(p, T);
-      a.w = P.qkv; a.scale = P.s_qkv; a.N = P.n_qkv; a.K = D; a.ld = D;
-      a.x = p->pxd; a.ldx = p->ld_xd; a.plane = plane_d; a.ssq = p->pssq;
-      a.y = p->pqkv; a.ldy = p->ld_qkv;
-      if (p->shared) a.sv = store_view(p, l, 0);
-      if ((st = run_kernel(tm, 0, s, [&] { return tasp::launch_pf_gemm(tasp::MM_QKV, a, s); })))
-        return st;
-    }
-    if (P.m_kv > 0) {
-      tasp::PfRopeArgs r{};
-      r.qkv = p->pqkv; r.ld_qkv = p->ld_qkv; r.ks = 1; r.m_q = P.m_q; r.m_kv = P.m_kv; r.dh = dh;
-      for (int q = 0; q < P.m_kv; ++q) r.kv_idx[q] = P.kv_idx[q];
-      r.kc = kc; r.vc = vc; r.S = cache->max_seq; r.rope_cos = p->rope_cos; r.rope_sin = p->rope_sin;
-      r.pos0 = pos0; r.T = T; r.q_out = p->pq; r.q_plane = plane_q; r.T_ld = Pm;
-      if ((st = run_kernel(tm, 7, s, [&] { return tasp::launch_pf_rope(r, s); }))) return st;
-      tasp::PfAttnArgs a{};
-      a.q = p->pq; a.q_plane = plane_q; a.T_ld = Pm; a.m_kv = P.m_kv; a.dh = dh;
-      for (int q = 0; q < P.m_kv; ++q) a.kv_idx[q] = P.kv_idx[q];
-      for (int q = 0; q <= P.m_kv; ++q) a.slot_start[q] = P.slot_start[q];
-      a.kc = kc; a.vc = vc; a.S = cache->max_seq; a.pos0 = pos0; a.T = T;
-      a.o_hl = p->pxw; a.ldo = p->ld_xw; a.o_plane = plane_w;
-      a.part = p->ppart; a.part_floats = p->ppart_floats; a.cnt = p->pacnt; a.cnt_len = p->pacnt_len;
-      if ((st = run_kernel(tm, 1, s, [&] { return tasp::launch_pf_attn(a, s); }))) return st;
-    }
-    {
-      tasp::PfArgs a = pf_base(p, T);
-      a.w = P.o; a.scale = P.s_o; a.N = D; a.K = P.m_q * dh; a.ld = P.ld_o;
-      a.x = p->pxw; a.ldx = p->ld_xw; a.plane = plane_w; a.resid = in; a.y = p->pr_mid; a.ldy = D;
-      a.gamma_next = P.fn; a.xo = p->pxd; a.ldxo = p->ld_xd; a.plane_o = plane_d; a.ssq_out = p->pssq;
-      if (p->shared) a.sv = store_view(p, l, 1);
-      if ((st = run_kernel(tm, 2, s, [&] { return tasp::launch_pf_gemm(tasp::MM_RESID, a, s); })))
-        return st;
-    }
-    if (P.c > 0) {
-      tasp::PfArgs a = pf_base(p, T);
-      if (p->shared) {
-        a.sv = store_view(p, l, 3);
-      } else {
-        a.w = P.g;
-        a.w2_off = uint32_t(reinterpret_cast<const char*>(P.u) - reinterpret_cast<const char*>(P.g));
-      }
-      a.scale = P.s_g; a.scale2 = P.s_u; a.N = P.c; a.K = D; a.ld = D;
-      a.x = p->pxd; a.ldx = p->ld_xd; a.plane = plane_d; a.ssq = p->pssq;
-      a.xo = p->pxw; a.ldxo = p->ld_xw; a.plane_o = plane_w;
-      if ((st = run_kernel(tm, 3, s, [&] { return tasp::launch_pf_gemm(tasp::MM_GATEUP, a, s); })))
-        return st;
-    }
-    {
-      tasp::PfArgs a = pf_base(p, T);
-      a.w = P.dn; a.scale = P.s_d; a.N = D; a.K = P.c; a.ld = P.ld_d;
-      a.x = p->pxw; a.ldx = p->ld_xw; a.plane = plane_w; a.resid = p->pr_mid; a.y = lo; a.ldy = D;
-      if (p->shared) a.sv = store_view(p, l, 4);
-      a.gamma_next = (l + 1 < L) ? p->layers[l + 1].an : (d.vocab ? p->final_norm : nullptr);
-      a.xo = p->pxd; a.ldxo = p->ld_xd; a.plane_o = plane_d; a.ssq_out = p->pssq;
-      if ((st = run_kernel(tm, 4, s, [&] { return tasp::launch_pf_gemm(tasp::MM_RESID, a, s); })))
-        return st;
     }
   }
   return d.vocab ? prefill_head(p, p->pr_io[(L - 1) & 1], T, out, s, tm, last_only) : TASP_OK;
@@ -1454,6 +1369,15 @@ tasp_status tasp_compile_shared_plan(const tasp_model_desc* desc, const tasp_gst
   if ((st = read_back_indices(p, c, Y, ws, s, h)) != TASP_OK) {
     delete p;
     return st;
+  }
+  for (LayerPlan& P : p->layers) {
+    P.o_chunks = P.d_chunks = 0;
+    int last = -1;
+    for (int h : P.q_idx)
+      if (h * dh / 128 != last) last = h * dh / 128, ++P.o_chunks;
+    last = -1;
+    for (int j : P.ffn_idx)
+      if (j / 128 != last) last = j / 128, ++P.d_chunks;
   }
   // the maps, checked against the host's reading of the index lists
   {

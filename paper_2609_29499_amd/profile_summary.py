@@ -44,12 +44,11 @@ def kind_of(name: str) -> str | None:
         (r"mfma_gemv_kernel<2,", "gateup_mfma"),
         (r"mfma_gemv_kernel<1,", "resid_mfma"),
         (r"mfma_gemv_kernel<3,", "lmhead_mfma"),
-        (r"pf_split_reduce_kernel<0>", "qkv_reduce"),
-        (r"pf_split_reduce_kernel<1>|pf_i8_reduce_kernel", "resid_reduce"),
-        (r"pf_(gemm|i8)_kernel<0,", "qkv_gemm"),
-        (r"pf_(gemm|i8)_kernel<2,", "gateup_gemm"),
-        (r"pf_(gemm|i8)_kernel<1,", "resid_gemm"),
-        (r"pf_gemm_kernel<3,", "lmhead_gemm"),
+        (r"pf_i8_reduce_kernel", "resid_reduce"),
+        (r"pf_i8_kernel<0,", "qkv_gemm"),
+        (r"pf_i8_kernel<2,", "gateup_gemm"),
+        (r"pf_i8_kernel<1,", "resid_gemm"),
+        (r"pf_head_kernel", "lmhead_gemm"),
         (r"router_features_kernel", "router_features"),
         (r"router_dense_kernel", "router_dense"),
         (r"router_head_kernel", "router_head"),

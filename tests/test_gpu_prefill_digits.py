@@ -84,3 +84,32 @@ def test_non_finite_rows():
         out = case.run()
         assert np.array_equal(np.delete(out, 6, 0), np.delete(got, 6, 0))
         assert not np.isfinite(out[6]).any()
+
+
+@pytest.mark.parametrize("dh,T", [(64, 5), (64, 70), (128, 40), (128, 200)])
+def test_groupwise_store(dh, T):
+    """The groupwise store with channel blocks of 16 and single dropped heads: with head_dim 64 a
+    store chunk of 128 columns holds a kept and a dropped head, the down projection's chunks hold
+    anything from one to eight blocks, and some chunks none."""
+    print(f"case digits groupwise dh={dh} T={T}", flush=True)
+    sh = synth.tiny_shape(d=512, hq=8, hkv=4, dh=dh, f=2048)
+    q, kv, f = synth.raw_mask(sh, 21, p_q=0.6, p_f=0.4, block=16)
+    f[:, 256:512] = 0
+    f[:, 1024:1040] = 1
+    case = PrefillCase(sh, (q, kv, f), T, 9, shared=True)
+    assert _rel(case.run(), case.oracle()) < REL
+
+
+@pytest.mark.parametrize("what", ["no_heads", "no_ffn", "wide"])
+def test_groupwise_store_edges(what):
+    """Empty modules, and the 128 x 256 tile shape with K splits."""
+    print(f"case digits groupwise {what}", flush=True)
+    wide = what == "wide"
+    sh = synth.tiny_shape(d=4096 if wide else 256, hq=8, hkv=2, dh=128 if wide else 64, f=8192 if wide else 512)
+    q, kv, f = synth.raw_mask(sh, 22, p_f=0.7, block=16)
+    if what == "no_heads":
+        q[:] = 0
+    elif what == "no_ffn":
+        f[:] = 0
+    case = PrefillCase(sh, (q, kv, f), 520 if wide else 33, 0, shared=True)
+    assert _rel(case.run(), case.oracle()) < REL
