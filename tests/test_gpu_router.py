@@ -86,6 +86,30 @@ def test_features_histogram_exact_and_scalars():
         assert np.array_equal(got[i, nb + 6:], want[6:]), f"prompt {i}: descriptors"
 
 
+@pytest.mark.parametrize("pat", [b"translat", b"TransLATe", b"```", b"\n1. go", b"\n12) go", b"\n123. go", b"\n1234. go",
+                                 b"\nA. x\n(B) y", b"(A) x\nB) y", b" who ", b" Whom ", b"\nWHERE?", b" which", b"=when4"])
+def test_pattern_at_every_offset(pat):
+    """Every position of a pattern inside the eight a thread examines, up to the end of the prompt,
+    for 1 to 9 prompts in a call (each count of prompts per workgroup of the layers)."""
+    _flush(f"case router offsets {pat!r}")
+    nb = 64
+    w = T.router_weights(seed=1, n_bins=nb, proj_dim=nb)
+    w["proj"] = np.eye(nb, dtype=np.float32)
+    texts = [_filler(o, o) + pat + _filler(e, o + 1) for o in range(18) for e in (0, 5)]
+    router = S.Router(w)
+    i = 0
+    for n in (1, 2, 3, 4, 5, 8, 9, 4):
+        part = texts[i:i + n]
+        i += n
+        f, _, _ = _route(router, part, np.full(n, -1.0))
+        for j, t in enumerate(part):
+            assert np.array_equal(f[j, :nb], (R.trigram_counts(t, nb) / max(1, len(t) - 2)).astype(np.float32)), t
+            want = R.features(t, -1.0, np.zeros((0, nb)), nb)
+            np.testing.assert_allclose(f[j, nb:nb + 6], want[:6], rtol=1e-6, atol=0)
+            assert np.array_equal(f[j, nb + 6:], want[6:]), t
+    assert i == len(texts)
+
+
 def test_boundary_prompts_raise_their_descriptor():
     # the fixtures above are meaningful only if each raises a descriptor or count in the oracle
     for t in _boundary_prompts():
