@@ -173,10 +173,15 @@ struct PfI8Args {
   // width, a multiple of 128: with a column map, 128 times the store chunks of 128 columns that
   // hold any retained column, listed by launch_pf_quant in x
   StoreView sv;
+  const uint8_t* list;                // operand whose first row holds that list (null: x)
 };
-// the tile shape and the number of K splits for these sizes
-void plan_pf_i8(MfmaMode mode, const PfI8Args& a, int* shape, int* ks);
-hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t s);
+// How a projection is launched: tile shape and K splits (ks of the arguments is set from it), or
+// (cut > 0) the first `cut` tokens with `shape` and the others with `shape2`
+struct PfI8Plan {
+  int shape, ks, cut, shape2;
+};
+PfI8Plan plan_pf_i8(MfmaMode mode, const PfI8Args& a);
+hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, const PfI8Plan& plan, hipStream_t s);
 // Digit rows o (PfI8Args::x layout, ldo bytes per digit) of the float32 rows x [T][ldx]. gamma:
 // the rows are x * gamma and the scale carries the inverse RMS of x. ks > 0: x is a residual
 // [T][K], the row is x + sum of part [ks][T][K], stored to y [T][K] as well. Without gamma and ks

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
   // whole chunks; with a column map the operand's chunk kc is the kc-th store chunk with any
   // retained column, listed behind the first token's scale.
   const bool mapped = SH && a.sv.cols != nullptr;
-  const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.x + 3 * size_t(a.ldx) + 16, mapped ? uint32_t(nk_all) * 4u : 0u);
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc((a.list ? a.list : a.x) + 3 * size_t(a.ldx) + 16, mapped ? uint32_t(nk_all) * 4u : 0u);
   auto clamp_chunk = [&](int kc) { return kc0 + max(min(kc, nk - 1), 0); };
   auto list_entry = [&](int kc) {                       // loaded one step before it is used
     return mapped ? __builtin_amdgcn_raw_buffer_load_b32(rl, 4 * clamp_chunk(kc), 0, 0) : 0u;
@@ -309,37 +309,50 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
     sc[nt] = SH ? 1.0f : (col[nt] < N ? (GU && nt >= NT / 2 ? a.scale2 : a.scale)[col[nt]] : 0.0f);
-  // the outputs through buffers (offsets past the end read zero and store nothing), the residuals
-  // of a row tile loaded together
+  // the outputs through buffers (offsets past the end read zero and store nothing); the residuals of
+  // the next row tile are loaded while one is stored (a load, a wait and a store per output chained
+  // 64 memory latencies)
   const bool split = a.ks > 1;
   const uint32_t ldo = split ? uint32_t(N) : uint32_t(a.ldy);
   float* const dst = split ? a.part + size_t(bz) * T * N : a.y;
-  const __amdgpu_buffer_rsrc_t ry = make_rsrc(dst, (uint32_t(T - 1) * ldo + uint32_t(N)) * 4u);
+  const uint32_t out_bytes = (uint32_t(T - 1) * ldo + uint32_t(N)) * 4u;
+  const __amdgpu_buffer_rsrc_t ry = make_rsrc(dst, out_bytes);
   const bool resid = MODE == MM_RESID && !split;
-  const __amdgpu_buffer_rsrc_t rr = make_rsrc(resid ? a.resid : nullptr, resid ? (uint32_t(T - 1) * ldo + uint32_t(N)) * 4u : 0u);
+  const __amdgpu_buffer_rsrc_t rr = make_rsrc(resid ? a.resid : nullptr, resid ? out_bytes : 0u);
   auto value = [&](int nt, int e, float tsc) {
     if constexpr (SH) return facc[nt][e] * tsc;
     else return join(acc[0][nt][e], acc[1][nt][e], acc[2][nt][e]) * tsc * sc[nt];
   };
+  auto token = [&](int e) { return wm * 32 + 8 * (e >> 2) + 4 * hi + (e & 3); };
+  auto offset = [&](int nt, int e) {
+    const int t = m0 + token(e);
+    return t < T && col[nt] < N ? (uint32_t(t) * ldo + uint32_t(col[nt])) * 4u : kOOB;
+  };
+  struct Resid {
+    float v[MODE == MM_RESID ? 16 : 1];
+  };
+  auto load_resid = [&](int nt) {
+    Resid q{};
+    if constexpr (MODE == MM_RESID) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        q.v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, int(offset(nt, e)), 0, 0));
+    }
+    return q;
+  };
+  Resid cur = load_resid(0), next{};
 #pragma unroll
   for (int nt = 0; nt < (GU ? NT / 2 : NT); ++nt) {
-    uint32_t off[16];
-    float tsc[16], res[16];
+    if (nt + 1 < NT) next = load_resid(nt + 1);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int tl = wm * 32 + 8 * (e >> 2) + 4 * hi + (e & 3), t = m0 + tl;
-      tsc[e] = ts[tl];
-      off[e] = t < T && col[nt] < N ? (uint32_t(t) * ldo + uint32_t(col[nt])) * 4u : kOOB;
-      if constexpr (MODE == MM_RESID)
-        res[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, int(off[e]), 0, 0));
+      const float tsc = ts[token(e)];
+      float v = value(nt, e, tsc);
+      if constexpr (GU) v = v / (1.0f + exp2f(-v * kLog2e)) * value(nt + NT / 2, e, tsc);
+      else if constexpr (MODE == MM_RESID) v += cur.v[e];
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), ry, int(offset(nt, e)), 0, 0);
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      float v = value(nt, e, tsc[e]);
-      if constexpr (GU) v = v / (1.0f + exp2f(-v * kLog2e)) * value(nt + NT / 2, e, tsc[e]);
-      else if constexpr (MODE == MM_RESID) v += res[e];
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), ry, int(off[e]), 0, 0);
-    }
+    cur = next;
   }
 }
 
@@ -507,15 +520,16 @@ constexpr float kFixedUs = 4.0f;        // launch, first chunk, epilogue
 constexpr int kMaxKSplit = 8;
 constexpr int kMinSplitChunks = 2;
 
-// expected time of a launch of w workgroups of n chunks each
-float launch_us(const Shape& h, long w, int n) {
+// expected time of a launch of w workgroups of n chunks each; a groupwise store's chunk takes about
+// 1.5 times as long (its vector work between the matrix passes)
+float launch_us(const Shape& h, long w, int n, bool store) {
   const long slots = long(kNumCu) * h.per_cu;
   auto chunk = [&](long u) {            // chunk time with u workgroups on the chip
     return u <= kNumCu ? h.t_one + (h.t_cu - h.t_one) * float(u) / kNumCu
                        : h.t_cu + (h.t_full - h.t_cu) * float(u - kNumCu) / float(slots - kNumCu);
   };
   const long rounds = w / slots, rest = w % slots;
-  return kFixedUs + float(n) * (float(rounds) * h.t_full + (rest ? chunk(rest) : 0.0f));
+  return kFixedUs + (store ? 1.5f : 1.0f) * float(n) * (float(rounds) * h.t_full + (rest ? chunk(rest) : 0.0f));
 }
 
 template <int MODE, bool SH>
@@ -545,36 +559,50 @@ hipError_t launch_quant(const PfQuantArgs& a, int width, hipStream_t s) {
 
 }  // namespace
 
-// The tile shape and K splits of least expected time (launch_us). A split adds its partial sums,
-// written here and read by the consumer (about 4 TB/s). Large shapes move fewer bytes per product;
-// small ones and splits fill the chip when there are few tokens: at 8 tokens the 8B down
-// projection takes 119 us on 32 x 1 workgroups of shape 0 and 11 us on 32 x 8 of shape 2, at 2048
-// tokens 184 us on shape 0 and 242 on shape 1.
-void plan_pf_i8(MfmaMode mode, const PfI8Args& a, int* shape, int* ks) {
+// The launch of least expected time (launch_us). A split adds its partial sums, written here and
+// read by the consumer (about 4 TB/s). Large shapes move fewer bytes per product; small ones and
+// splits fill the chip when there are few tokens: at 8 tokens the 8B down projection takes 119 us
+// on 32 x 1 workgroups of shape 0 and 11 us on 32 x 8 of shape 2, at 2048 tokens 184 us on shape 0
+// and 242 on shape 1. Without splits the tokens may be cut in two launches, the first of whole
+// rounds of shape 0, so that the last round is not mostly empty (8B gate/up at 700 tokens: 384
+// tiles of shape 0 are one and a half rounds, 158 us, 144 us on shape 1; 512 tokens in one round of
+// shape 0 and 188 on shape 1, 136 us).
+PfI8Plan plan_pf_i8(MfmaMode mode, const PfI8Args& a) {
   const int chunks = (a.K + kKC - 1) / kKC;
+  const bool store = a.sv.gs != nullptr;
   const bool can_split = mode != MM_GATEUP && a.part && a.N > 0;
   const long room = can_split ? long(a.part_floats / (size_t(a.T) * a.N)) : 1;
   const int max_ks = can_split ? int(std::max(1l, std::min({long(kMaxKSplit), long(chunks / kMinSplitChunks), room}))) : 1;
-  float best = 0.0f;
-  *shape = 0;
-  *ks = 1;
-  for (int i = 0; i < 3; ++i) {
-    const Shape& h = kShapes[i];
-    const int rows = mode == MM_GATEUP ? h.tn / 2 : h.tn;
-    const long tiles = long((a.N + rows - 1) / rows) * ((a.T + h.tm - 1) / h.tm);
+  auto tiles = [&](int i, int T) {
+    const int rows = mode == MM_GATEUP ? kShapes[i].tn / 2 : kShapes[i].tn;
+    return long((a.N + rows - 1) / rows) * ((T + kShapes[i].tm - 1) / kShapes[i].tm);
+  };
+  PfI8Plan best{0, 1, 0, 0};
+  float best_us = 3e38f;
+  for (int i = 0; i < 3; ++i)
     for (int k = 1; k <= max_ks; ++k) {
-      const float us = launch_us(h, tiles * k, (chunks + k - 1) / k) +
+      const float us = launch_us(kShapes[i], tiles(i, a.T) * k, (chunks + k - 1) / k, store) +
                        (k > 1 ? float(k) * float(a.T) * float(a.N) * 4.0f * 2.0f / 4e6f : 0.0f);
-      if ((i == 0 && k == 1) || us < best) {
-        best = us;
-        *shape = i;
-        *ks = k;
+      if (us < best_us) {
+        best_us = us;
+        best = PfI8Plan{i, k, 0, 0};
+      }
+    }
+  for (int cut = kShapes[0].tm; cut < a.T; cut += kShapes[0].tm) {
+    const float head = launch_us(kShapes[0], tiles(0, cut), chunks, store);
+    for (int i = 1; i < 3; ++i) {
+      const float us = head + launch_us(kShapes[i], tiles(i, a.T - cut), chunks, store);
+      if (us < 0.95f * best_us) {
+        best_us = us;
+        best = PfI8Plan{0, 1, cut, i};
       }
     }
   }
+  return best;
 }
 
-hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t s) {
+namespace {
+hipError_t launch_part(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t s) {
   if (a.sv.gs) {
     // store rows in whole chunks, one scale group each
     if (a.K % kKC != 0 || a.sv.ld % kKC != 0 || a.K > a.sv.ld || a.sv.store_rows < 1 ||
@@ -596,6 +624,24 @@ hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t
     case MM_GATEUP: return sh ? launch_mode<MM_GATEUP, true>(a, shape, s) : launch_mode<MM_GATEUP, false>(a, shape, s);
     default: return hipErrorInvalidValue;
   }
+}
+}  // namespace
+
+hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a0, const PfI8Plan& plan, hipStream_t s) {
+  PfI8Args a = a0;
+  a.ks = plan.ks;
+  if (plan.cut <= 0) return launch_part(mode, a, plan.shape, s);
+  if (plan.cut >= a.T || plan.ks != 1) return hipErrorInvalidValue;
+  a.T = plan.cut;
+  const hipError_t e = launch_part(mode, a, plan.shape, s);
+  if (e != hipSuccess) return e;
+  // the other tokens (a column-mapped operand's chunk list stays behind the first token's scale)
+  a.list = a0.list ? a0.list : a0.x;
+  a.x = a0.x + size_t(plan.cut) * 4 * a.ldx;
+  if (a.resid) a.resid += size_t(plan.cut) * a.ldy;
+  a.y += size_t(plan.cut) * a.ldy;
+  a.T = a0.T - plan.cut;
+  return launch_part(mode, a, plan.shape2, s);
 }
 
 hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s) {

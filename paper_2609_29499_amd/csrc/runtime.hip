@@ -694,10 +694,10 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
   float* wide = reinterpret_cast<float*>(p->pxw);
   tasp_status st;
   auto gemm = [&](int kind, tasp::MfmaMode mode, tasp::PfI8Args& a) {
-    int shape = 0;
     a.T = T; a.part = p->ppart; a.part_floats = p->ppart_floats;
-    tasp::plan_pf_i8(mode, a, &shape, &a.ks);
-    return run_kernel(tm, kind, s, [&] { return tasp::launch_pf_i8(mode, a, shape, s); });
+    const tasp::PfI8Plan plan = tasp::plan_pf_i8(mode, a);
+    a.ks = plan.ks;
+    return run_kernel(tm, kind, s, [&] { return tasp::launch_pf_i8(mode, a, plan, s); });
   };
   // digits of (r [+ the ks splits' sum, stored to y]) * gamma into pxd
   auto quant_norm = [&](const float* r, const uint16_t* gamma, int ks, float* y) {

@@ -47,6 +47,18 @@ def test_widths(d, hq, hkv, dh, f, T):
     assert _rel(case.run(), case.oracle()) < REL
 
 
+@pytest.mark.parametrize("shared,d,f,T", [(False, 4096, 8192, 600), (True, 4096, 8192, 600), (True, 8192, 2048, 1200)])
+def test_cut_launch(shared, d, f, T):
+    """Token counts at which a projection is cut in two launches (whole rounds of 128 x 256 tiles, then
+    smaller ones): gate/up with about 7950 channels at 600 tokens, and the column-mapped down
+    projection of 8192 rows at 1200 tokens, whose chunk list stays behind the first launch's first
+    token."""
+    print(f"case digits cut shared={shared} d={d} f={f} T={T}", flush=True)
+    sh = synth.tiny_shape(d=d, hq=4, hkv=2, dh=64, f=f)
+    case = PrefillCase(sh, synth.raw_mask(sh, 3, p_f=0.97, block=16), T, 0, shared=shared)
+    assert _rel(case.run(), case.oracle()) < REL
+
+
 def test_number_range():
     """Rows of zeros, of tiny and of large values, and rows with one value far above the rest: each
     token has its own scale, so a token's result does not depend on its neighbours, and its error
