@@ -34,8 +34,18 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int kStepsPerBatch = 4;      // 16-row weight loads per lane and load batch
 constexpr int kNumCu = 256;
-constexpr int kMmTwoTileRows = 8192;   // panels at least this tall use two row tiles per wave
-constexpr int kMmFourTileRows = 15360; // and four from here (240 tiles of 64 rows: every CU but 16 busy)
+// Row tiles per wave. Each activation fragment feeds all of a wave's row tiles, so tall panels take
+// two (from 6144 rows: 192 tiles of 32 rows on 256 CUs; the 6144 x 8192 QKV panel at batch 4 23.5 ->
+// 20.1 us, a 7776 x 2064 gate/up at batch 3 12.1 -> 10.6, while the 3840 x 4096 QKV panel goes from
+// 10.4 to 12.5). Residual projections have long rows in few tiles and take two from 8192 rows (4096 x
+// 8192 at batch 4: 13.9 -> 18.4 us with two), below that one tile on four waves (eight: 14.6). Gate/up
+// panels of at least 15360 rows (240 tiles of 64 rows: every CU but 16 busy) take four at batches of
+// 7 and 8 (8B at batch 8 23.6 -> 22.7 us, 70B 78.5 -> 73.9), where operand reads weigh most; smaller
+// batches are faster with two (8B at batch 2 21.1 -> 19.6 us, 70B at batch 4 70.3 -> 66.6).
+constexpr int kMmTwoTileRows = 6144;
+constexpr int kMmTwoTileResidRows = 8192;
+constexpr int kMmFourTileRows = 15360;
+constexpr int kMmFourTileBatch = 7;
 constexpr int kSsqBatch = 8;           // sums-of-squares partials loaded per thread and round
 
 // Two float32 holding values exact in BF16 -> packed BF16 pair (lo in the low half).
@@ -398,18 +408,17 @@ hipError_t launch_mm(const MfmaArgs& a, hipStream_t s) {
 
 template <int MODE>
 hipError_t launch_mm_mode(const MfmaArgs& a, hipStream_t s) {
-  // two row tiles per wave halve the activation reads per weight byte; panels with few rows
-  // keep one so that every CU gets a tile, with more waves per tile so that enough loads fly
   const int rows = (MODE == MM_GATEUP) ? 2 * a.N : a.N;
+  const bool two = rows >= (MODE == MM_RESID ? kMmTwoTileResidRows : kMmTwoTileRows);
   if constexpr (MODE != MM_LMHEAD) {
-    if (a.sv.gs) {
-      if (rows >= kMmTwoTileRows) return launch_mm<MODE, 4, 2, true>(a, s);
-      return launch_mm<MODE, 8, 1, true>(a, s);
-    }
+    // (the store's widened weights weigh more than the operand: no four-tile form, and one tile on
+    // eight waves: 8B QKV at batch 4 13.5 us, on four 13.8; O 11.4 and 11.8)
+    if (a.sv.gs) return two ? launch_mm<MODE, 4, 2, true>(a, s) : launch_mm<MODE, 8, 1, true>(a, s);
   }
-  // four row tiles for the tallest panels (the 8B gate/up at batch 8: 23.1 -> 22.1 us)
-  if (MODE == MM_GATEUP && rows >= kMmFourTileRows) return launch_mm<MODE, 4, 4, false>(a, s);
-  if (rows >= kMmTwoTileRows) return launch_mm<MODE, 4, 2, false>(a, s);
+  if (MODE == MM_GATEUP && rows >= kMmFourTileRows && a.B >= kMmFourTileBatch)
+    return launch_mm<MODE, 4, 4, false>(a, s);
+  if (two) return launch_mm<MODE, 4, 2, false>(a, s);
+  if (MODE == MM_RESID) return launch_mm<MODE, 4, 1, false>(a, s);
   return launch_mm<MODE, 8, 1, false>(a, s);
 }
 
