@@ -14,11 +14,12 @@
 // registers while the current one is computed; one barrier per sub-block. Per 16-row tile:
 //   * S^T = K Q^T on v_mfma_f32_16x16x32_bf16: K rows are the A operand, q (hi/lo BF16 planes, in
 //     base-2 units: q carries log2(e) / sqrt(d_h)) the B operand, so lane (r, c) receives the
-//     scores of query r against rows 4 c .. 4 c + 3 of the tile, which is exactly the A-operand
-//     layout of v_mfma_f32_16x16x16_bf16: P never leaves the registers;
+//     scores of query r against rows 4 c .. 4 c + 3 of the tile: P never leaves the registers;
 //   * causal mask, online softmax per query (the query's four lanes exchange maxima and sums by
 //     lane permutes);
-//   * O += P V on v_mfma_f32_16x16x16_bf16 with P split into hi/lo BF16 and V units read from LDS;
+//   * O += P V on v_mfma_f32_16x16x32_bf16 over pairs of tiles with P split into hi/lo BF16 and V
+//     units read from LDS: lane c's eight k are rows 4 c .. + 3 of both tiles, on either side (the
+//     16-deep form takes the same time for half the products);
 //     the output holds query 4 c + i in lane (r, c), so the per-query rescale factors move there
 //     by a lane permute.
 // The output O / l is written in float32.
@@ -32,7 +33,6 @@ namespace {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-typedef short __attribute__((ext_vector_type(4))) s16x4;
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
@@ -48,6 +48,11 @@ struct PaSmem {
 
 __device__ __forceinline__ uint32_t cvt_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+
+// two four-element pieces as one eight-element operand
+__device__ __forceinline__ bf16x8 pair8(const uint2& a, const uint2& b) {
+  return __builtin_bit_cast(bf16x8, make_int4(int(a.x), int(a.y), int(b.x), int(b.y)));
 }
 
 // 4-byte device-coherent accesses (cache-policy bit sc1, as the 16-byte ones of the common
@@ -228,7 +233,7 @@ __global__ __launch_bounds__(kBlock) void pf_attn_kernel(PfAttnArgs a) {
     const float mn = fmaxf(m_run, mx);
     const float base = mn == -INFINITY ? 0.0f : mn;     // a query with no row yet stays empty
     float ps = 0.0f;
-    s16x4 ph[4], pl[4];
+    uint2 ph[4], pl[4];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
       float pv4[4];
@@ -240,8 +245,8 @@ __global__ __launch_bounds__(kBlock) void pf_attn_kernel(PfAttnArgs a) {
       const uint32_t h0 = cvt_bf16x2(pv4[0], pv4[1]), h1 = cvt_bf16x2(pv4[2], pv4[3]);
       const uint32_t l0 = cvt_bf16x2(pv4[0] - bf16_lo(h0), pv4[1] - bf16_hi(h0));
       const uint32_t l1 = cvt_bf16x2(pv4[2] - bf16_lo(h1), pv4[3] - bf16_hi(h1));
-      ph[ct] = __builtin_bit_cast(s16x4, make_uint2(h0, h1));
-      pl[ct] = __builtin_bit_cast(s16x4, make_uint2(l0, l1));
+      ph[ct] = make_uint2(h0, h1);
+      pl[ct] = make_uint2(l0, l1);
     }
     ps = quad_sum(ps);
     const float alpha = __builtin_amdgcn_exp2f(m_run - base);   // 0 while m_run is -inf
@@ -256,13 +261,13 @@ __global__ __launch_bounds__(kBlock) void pf_attn_kernel(PfAttnArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[d][i] *= al[i];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
+    for (int ct = 0; ct < 4; ct += 2)
 #pragma unroll
       for (int d = 0; d < NDT; ++d) {
-        const s16x4 vb = __builtin_bit_cast(
-            s16x4, *reinterpret_cast<const uint2*>(&sm.vt[buf][(16 * d + r) * kVtRow + 16 * ct + 4 * c]));
-        o[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ph[ct], vb, o[d], 0, 0, 0);
-        o[d] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pl[ct], vb, o[d], 0, 0, 0);
+        const uint16_t* vt = &sm.vt[buf][(16 * d + r) * kVtRow + 16 * ct + 4 * c];
+        const bf16x8 vb = pair8(*reinterpret_cast<const uint2*>(vt), *reinterpret_cast<const uint2*>(vt + 16));
+        o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pair8(ph[ct], ph[ct + 1]), vb, o[d], 0, 0, 0);
+        o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pair8(pl[ct], pl[ct + 1]), vb, o[d], 0, 0, 0);
       }
   }
 
