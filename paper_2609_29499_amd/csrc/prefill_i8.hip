@@ -398,6 +398,7 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
     __syncthreads();
     kz = n_chunks * kKC;
   }
+  const __amdgpu_buffer_rsrc_t rp = make_rsrc(a.part, uint32_t(a.ks) * uint32_t(a.T) * uint32_t(K) * 4u);
   float4 v[NV];
   float amax = 0.0f, ss = 0.0f;
 #pragma unroll
@@ -415,9 +416,11 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
     }
     const f32x4u xv = *reinterpret_cast<const f32x4u*>(a.x + size_t(t) * a.ldx + src);
     v[j] = make_float4(xv.x, xv.y, xv.z, xv.w);
-    for (int z = 0; z < a.ks; ++z) {
-      const float4 p = *reinterpret_cast<const float4*>(a.part + (size_t(z) * a.T + t) * K + k);
-      v[j].x += p.x; v[j].y += p.y; v[j].z += p.z; v[j].w += p.w;
+    if (a.ks) {
+      const uint32_t off[1] = {(uint32_t(t) * uint32_t(K) + uint32_t(k)) * 4u};
+      float4 sum[1] = {v[j]};
+      add_splits(rp, off, uint32_t(a.T) * uint32_t(K) * 4u, 0, a.ks, sum);
+      v[j] = sum[0];
     }
     if (a.ks) *reinterpret_cast<float4*>(a.y + size_t(t) * K + k) = v[j];
     if (a.gamma) {
@@ -499,12 +502,11 @@ __global__ __launch_bounds__(kBlock) void pf_i8_reduce_kernel(const float* __res
                                                               int T, int N) {
   const int t = blockIdx.y, n = 4 * (blockIdx.x * kBlock + threadIdx.x);
   if (n >= N) return;
-  f32x4u v = *reinterpret_cast<const f32x4u*>(resid + size_t(t) * N + n);
-  for (int z = 0; z < ks; ++z) {
-    const float4 p = *reinterpret_cast<const float4*>(part + (size_t(z) * T + t) * N + n);
-    v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
-  }
-  *reinterpret_cast<f32x4u*>(y + size_t(t) * N + n) = v;
+  const f32x4u r = *reinterpret_cast<const f32x4u*>(resid + size_t(t) * N + n);
+  float4 v[1] = {make_float4(r.x, r.y, r.z, r.w)};
+  const uint32_t stride = uint32_t(T) * uint32_t(N) * 4u, off[1] = {(uint32_t(t) * uint32_t(N) + uint32_t(n)) * 4u};
+  add_splits(make_rsrc(part, uint32_t(ks) * stride), off, stride, 0, ks, v);
+  *reinterpret_cast<f32x4u*>(y + size_t(t) * N + n) = f32x4u{v[0].x, v[0].y, v[0].z, v[0].w};
 }
 
 struct Shape {
@@ -655,12 +657,16 @@ hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s) {
     return a.store_cols <= 4 * 256 * 7 ? launch_quant<256, true>(a, a.store_cols, s)
                                        : launch_quant<1024, true>(a, a.store_cols, s);
   }
-  return a.K <= 4 * 256 * 7 ? launch_quant<256, false>(a, a.K, s) : launch_quant<1024, false>(a, a.K, s);
+  if (size_t(a.ks) * a.T * a.K * 4 >= size_t(kOOB)) return hipErrorInvalidValue;
+  // wide rows, and short prompts (at most a workgroup per CU, each a chain of its own loads), on more
+  // threads: 16 rows of 4096 and eight splits took 12 us on 256 threads with a wait per split, 4.6 now
+  return a.K <= 4 * 256 * 7 && (a.T > kNumCu || a.K <= 1024) ? launch_quant<256, false>(a, a.K, s)
+                                                            : launch_quant<1024, false>(a, a.K, s);
 }
 
 hipError_t launch_pf_i8_reduce(const float* part, int ks, const float* resid, float* y, int T, int N,
                                hipStream_t s) {
-  if (N % 4 != 0 || T < 1) return hipErrorInvalidValue;
+  if (N % 4 != 0 || T < 1 || ks < 0 || size_t(ks) * T * N * 4 >= size_t(kOOB)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(pf_i8_reduce_kernel, dim3((N / 4 + kBlock - 1) / kBlock, T), dim3(kBlock), 0, s, part, ks,
                      resid, y, T, N);
   return hipGetLastError();
