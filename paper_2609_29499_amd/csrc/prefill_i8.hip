@@ -21,7 +21,8 @@
 // channel in one wave); each wave holds its outputs, times three digits, in registers. K advances
 // in chunks of 128, one memory line per row: digit rows and panel rows go from memory straight
 // into two LDS stages (buffer loads with an LDS destination, 16-byte pieces XOR-swizzled by row on
-// the memory side), the next chunk in flight while one is multiplied, one barrier per chunk.
+// the memory side), the next chunk in flight while one is multiplied, one barrier per chunk. Where few
+// tiles leave a CU one workgroup, its waves deal the chunks among groups (KW below).
 //
 // Groupwise store (shared-store plans). A chunk of 128 columns is one scale group, so the three digit
 // sums of a chunk are exact integers that meet one BF16 scale: 256 d2 + d1 is formed in one int32
@@ -71,12 +72,6 @@ __device__ __forceinline__ float join(int s2, int s1, int s0) {
   return fmaf(float(s2), 65536.0f, fmaf(float(s1), 256.0f, float(s0)));
 }
 
-template <int TM, int TN>
-struct I8Stage {
-  uint8_t a[3 * TM * kKC];               // digit planes, token rows of kKC bytes
-  uint8_t b[TN * kKC];                   // panel rows of kKC bytes
-};
-
 // Workgroup id -> (n tile, m tile, split). Ids go round-robin over the XCDs; each XCD takes a
 // contiguous run of an order that walks kGroupM token tiles together, so that the workgroups an
 // XCD holds at one time share digit and panel rows in its L2.
@@ -92,21 +87,34 @@ __device__ __forceinline__ void tile_of(int id, int total, int gx, int gy, int& 
   bx = in / gm;
 }
 
-// NT tiles of 32 tokens x 32 rows per wave; WGM x WGN waves; WAVES: per SIMD; SH: groupwise store
-template <int MODE, int NT, int WGM, int WGN, int WAVES, bool SH>
-__global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a, int gx, int gy) {
+// NT tiles of 32 tokens x 32 rows per wave; WGM x WGN waves; WAVES: per SIMD; SH: groupwise store.
+// KW > 1: KW groups of WGM x WGN waves share the tile, group kw multiplying chunks kw, kw + KW, .. from
+// stages of its own (without a barrier where a group is one wave), and their digit sums meet in LDS.
+// With one workgroup per CU a chunk costs its latency and not its products; KW chunks are in flight
+// instead of one (8B layer: gate/up at 16 tokens 26.5 us on 32 x 128 tiles, 15 on 32 x 64 with four
+// groups; at 128 tokens 33 us on 64 x 128 tiles, 29 with two groups; down at 512 tokens 61 and 54).
+template <int MODE, int NT, int WGM, int WGN, int KW, int WAVES, bool SH>
+__global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8Args a, int gx, int gy) {
   constexpr bool GU = (MODE == MM_GATEUP);
   constexpr int HN = 16 * NT;                           // gate/up: channels per wave
   constexpr int TM = 32 * WGM, TN = 32 * NT * WGN, NW = WGM * WGN;
+  constexpr int EC = 16 / KW;                           // outputs per row tile and lane
   constexpr int RPL = 1024 / kKC, LPR = kKC / 16;       // rows per 1 KiB load, lanes per row
   constexpr int APER = 3 * TM / RPL / NW, BPER = TN / RPL / NW;
   static_assert(APER * RPL * NW == 3 * TM && BPER * RPL * NW == TN, "even share of the loads");
   static_assert(HN % (RPL * NW) == 0, "a panel load of a wave lies in gate or in up rows, the same for every wave");
   static_assert(TM <= 64 * NW, "one token scale per thread");
-  __shared__ __attribute__((aligned(16))) I8Stage<TM, TN> st0;
-  __shared__ __attribute__((aligned(16))) I8Stage<TM, TN> st1;
+  static_assert(KW == 1 || KW == 2 || KW == 4, "the groups share a lane's 16 outputs of a row tile by fours");
+  // A group's stage: the digit planes' token rows of kKC bytes, then the panel rows. Each stage is one
+  // flat array indexed by one sum, so that the compiler tells the two apart (through members of nested
+  // objects it loses track and makes a read of one wait for the loads into the other).
+  constexpr int SA = 3 * TM * kKC, SB = TN * kKC, SBYTES = SA + SB;
+  typedef uint8_t Stage[KW * SBYTES];
+  __shared__ __attribute__((aligned(16))) Stage st0;
+  __shared__ __attribute__((aligned(16))) Stage st1;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = KW > 1 ? wave_id / NW : 0, wave = wave_id - kw * NW;   // group, wave of it
   const int r = lane & 31, hi = lane >> 5;
   const int wm = wave / WGN, wn = wave % WGN;
   const int T = a.T, N = a.N;
@@ -150,22 +158,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
   // retained column, listed behind the first token's scale.
   const bool mapped = SH && a.sv.cols != nullptr;
   const __amdgpu_buffer_rsrc_t rl = make_rsrc((a.list ? a.list : a.x) + 3 * size_t(a.ldx) + 16, mapped ? uint32_t(nk_all) * 4u : 0u);
-  auto clamp_chunk = [&](int kc) { return kc0 + max(min(kc, nk - 1), 0); };
+  auto clamp_chunk = [&](int kc) { return kc0 + max(min(kw + KW * kc, nk - 1), 0); };
   auto list_entry = [&](int kc) {                       // loaded one step before it is used
     return mapped ? __builtin_amdgcn_raw_buffer_load_b32(rl, 4 * clamp_chunk(kc), 0, 0) : 0u;
   };
   auto store_chunk = [&](int kc, uint32_t entry) {
     return mapped ? int(__builtin_amdgcn_readfirstlane(int(entry))) : clamp_chunk(kc);
   };
-  auto issue = [&](int kc, int wc, I8Stage<TM, TN>& S) {
-    const int k0 = clamp_chunk(kc) * kKC, kw = SH ? wc * kKC : k0;
+  auto issue = [&](int kc, int wc, Stage& S) {
+    const int k0 = clamp_chunk(kc) * kKC, wk = SH ? wc * kKC : k0;
 #pragma unroll
     for (int j = 0; j < APER; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S.a[(wave + NW * j) * 1024]), 16, int(abase[j]), k0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S[kw * SBYTES + (wave + NW * j) * 1024]), 16, int(abase[j]), k0, 0, 0);
 #pragma unroll
     for (int j = 0; j < BPER; ++j) {
       const __amdgpu_buffer_rsrc_t rj = SH && up_load(j) ? rw2 : rw;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rj, static_cast<void*>(&S.b[(wave + NW * j) * 1024]), 16, int(bbase[j]), kw, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rj, static_cast<void*>(&S[kw * SBYTES + SA + (wave + NW * j) * 1024]), 16, int(bbase[j]), wk, 0, 0);
     }
   };
 
@@ -226,15 +234,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
 #pragma unroll
     for (int e = 0; e < 16; ++e) facc[j][e] = 0.0f;
 
-  auto frag_a = [&](const I8Stage<TM, TN>& S, int d, int ks) {   // (tile rows differ from r by multiples of 32)
-    return *reinterpret_cast<const i32x4*>(&S.a[d * TM * kKC + (wm * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
+  auto frag_a = [&](const Stage& S, int d, int ks) {   // (tile rows differ from r by multiples of 32)
+    return *reinterpret_cast<const i32x4*>(&S[kw * SBYTES + d * TM * kKC + (wm * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
   };
-  auto frag_b = [&](const I8Stage<TM, TN>& S, int nt, int ks) {
-    return *reinterpret_cast<const i32x4*>(&S.b[((wn * NT + nt) * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
+  auto frag_b = [&](const Stage& S, int nt, int ks) {
+    return *reinterpret_cast<const i32x4*>(&S[kw * SBYTES + SA + ((wn * NT + nt) * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
   };
-  auto compute = [&](const I8Stage<TM, TN>& S, const Scales& sv) {
+  auto compute = [&](const Stage& S, const Scales& sv) {
     if constexpr (!SH) {
-#pragma unroll 2
+#pragma unroll (KW > 1 ? 4 : 2)
       for (int ks = 0; ks < kKC / 32; ++ks) {
         i32x4 bf[NT];
 #pragma unroll
@@ -285,26 +293,85 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
   // chunk kc sits in stage kc % 2: wait for this wave's loads of it, meet the other waves (their
   // loads of it have landed, and all of them are done with the other stage), load the next chunk
   // into the other stage, multiply
-  auto step = [&](int kc, const I8Stage<TM, TN>& cur, I8Stage<TM, TN>& nxt, const Scales& sv, Scales& sn) {
-    wait_vm0();
-    __builtin_amdgcn_s_barrier();
+  auto step = [&](int kc, const Stage& cur, Stage& nxt, const Scales& sv, Scales& sn) {
+    if constexpr (KW > 1 && NW == 1) {
+      __builtin_amdgcn_s_waitcnt(0);                    // (and its reads of the other stage are done)
+      asm volatile("" ::: "memory");
+    } else {
+      wait_vm0();
+      __builtin_amdgcn_s_barrier();
+    }
     const int wc = store_chunk(kc + 1, entry);
     entry = list_entry(kc + 2);
     if constexpr (SH) sn = load_scales(wc);
     issue(kc + 1, wc, nxt);
-    compute(cur, sv);
+    if (KW == 1 || kw + KW * kc < nk) compute(cur, sv);
   };
-  for (int kc = 0; kc < nk; kc += 2) {
+  const int nkw = (nk + KW - 1) / KW;                   // steps, the same for every group
+  for (int kc = 0; kc < nkw; kc += 2) {
     step(kc, st0, st1, sc0, sc1);
-    if (kc + 1 < nk) step(kc + 1, st1, st0, sc1, sc0);
+    if (kc + 1 < nkw) step(kc + 1, st1, st0, sc1, sc0);
   }
   wait_vm0();
   __syncthreads();                                      // every wave is done with the stages
-  float* ts = reinterpret_cast<float*>(&st0);
+  // Token scales, and (KW > 1) the groups' sums: group kw adds up outputs EC kw .. + EC - 1 of every
+  // lane and row tile, the others leave theirs in LDS (32 KiB per digit, two in st0, one in st1).
+  constexpr int ND = SH ? 1 : 3, QG = 4 / KW;           // digits, groups of four outputs per wave group
+  constexpr int QS = KW == 2 ? 2 : 4;                   // groups of four a wave leaves (KW 4: its own unused)
+  constexpr size_t kSumBytes = KW > 1 ? size_t(KW) * NW * NT * QS * kWave * 16 : 0;   // of one digit
+  static_assert((ND > 1 ? 2 : 1) * kSumBytes <= sizeof(st0) && kSumBytes + TM * 4 <= sizeof(st1), "the sums fit the stages");
+  float* ts = reinterpret_cast<float*>(reinterpret_cast<char*>(&st1) + kSumBytes);
   if (tid < TM) ts[tid] = tscale;
+  auto sums = [&](int d, int k, int nt, int g) -> i32x4* {
+    char* base = d < 2 ? reinterpret_cast<char*>(&st0) + size_t(d) * kSumBytes : reinterpret_cast<char*>(&st1);
+    return reinterpret_cast<i32x4*>(base) + (((k * NW + wave) * NT + nt) * QS + g % QS) * kWave + lane;
+  };
+  auto bits = [&](int d, int nt, int e) {
+    if constexpr (SH) return __float_as_int(facc[nt][e]);
+    else return int(acc[d][nt][e]);
+  };
+  if constexpr (KW > 1) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          if (g / QG != kw) *sums(d, kw, nt, g) = i32x4{bits(d, nt, 4 * g), bits(d, nt, 4 * g + 1), bits(d, nt, 4 * g + 2), bits(d, nt, 4 * g + 3)};
+  }
   __syncthreads();
+  if constexpr (KW > 1) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int g = 0; g < QG; ++g) {
+          i32x4 v[KW];
+#pragma unroll
+          for (int k = 0; k < KW; ++k) {
+            v[k] = i32x4{bits(d, nt, EC * k + 4 * g), bits(d, nt, EC * k + 4 * g + 1), bits(d, nt, EC * k + 4 * g + 2), bits(d, nt, EC * k + 4 * g + 3)};
+            if (k != kw) v[k] = *sums(d, k, nt, QG * kw + g);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if constexpr (SH) {
+              float f = __int_as_float(v[0][i]);
+#pragma unroll
+              for (int k = 1; k < KW; ++k) f += __int_as_float(v[k][i]);
+              facc[nt][4 * g + i] = f;
+            } else {
+              int q = v[0][i];
+#pragma unroll
+              for (int k = 1; k < KW; ++k) q += v[k][i];
+              acc[d][nt][4 * g + i] = q;
+            }
+          }
+        }
+  }
 
   // ---- epilogue: lane (r, hi) holds tokens 8 g + 4 hi + i of the token tile for row r
+  // (KW > 1: outputs EC kw .. of each row tile)
   float sc[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
@@ -323,19 +390,19 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
     if constexpr (SH) return facc[nt][e] * tsc;
     else return join(acc[0][nt][e], acc[1][nt][e], acc[2][nt][e]) * tsc * sc[nt];
   };
-  auto token = [&](int e) { return wm * 32 + 8 * (e >> 2) + 4 * hi + (e & 3); };
+  auto token = [&](int e) { return wm * 32 + 8 * ((EC * kw + e) >> 2) + 4 * hi + (e & 3); };
   auto offset = [&](int nt, int e) {
     const int t = m0 + token(e);
     return t < T && col[nt] < N ? (uint32_t(t) * ldo + uint32_t(col[nt])) * 4u : kOOB;
   };
   struct Resid {
-    float v[MODE == MM_RESID ? 16 : 1];
+    float v[MODE == MM_RESID ? EC : 1];
   };
   auto load_resid = [&](int nt) {
     Resid q{};
     if constexpr (MODE == MM_RESID) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
+      for (int e = 0; e < EC; ++e)
         q.v[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rr, int(offset(nt, e)), 0, 0));
     }
     return q;
@@ -345,7 +412,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WAVES) void pf_i8_kernel(PfI8Args a
   for (int nt = 0; nt < (GU ? NT / 2 : NT); ++nt) {
     if (nt + 1 < NT) next = load_resid(nt + 1);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
+    for (int e = 0; e < EC; ++e) {
       const float tsc = ts[token(e)];
       float v = value(nt, e, tsc);
       if constexpr (GU) v = v / (1.0f + exp2f(-v * kLog2e)) * value(nt + NT / 2, e, tsc);
@@ -510,28 +577,34 @@ __global__ __launch_bounds__(kBlock) void pf_i8_reduce_kernel(const float* __res
 }
 
 struct Shape {
-  int tm, tn, per_cu;
-  float t_one, t_cu, t_full;            // us per chunk: few workgroups, one per CU, per_cu per CU
+  int tm, tn, kw, per_cu;
+  float fixed;                          // us: launch, first chunk, epilogue
+  float t_one, t_cu, t_full;            // us per step: few workgroups, one per CU, per_cu per CU
+  float store;                          // factor of a groupwise store (vector work between the passes)
 };
 // 0: 128 x 256, eight waves of 32 x 128; 1: 64 x 128, four waves of 32 x 64; 2: 32 x 128, two waves
-// of 32 x 64. The chunk times are measured (8B and 70B gate/up and down at 8 to 2048 tokens).
-constexpr Shape kShapes[3] = {{128, 256, 1, 1.9f, 2.65f, 2.65f},
-                              {64, 128, 2, 0.85f, 0.94f, 1.52f},
-                              {32, 128, 2, 0.65f, 0.75f, 1.30f}};
-constexpr float kFixedUs = 4.0f;        // launch, first chunk, epilogue
+// of 32 x 64; 3: 32 x 64, four waves, each with every fourth chunk; 4: as 1, two groups of four waves,
+// each with every other chunk. A step is a chunk per group. The times are measured (8B and 70B
+// projections at 8 to 2048 tokens, each shape with 1 to 8 splits).
+constexpr int kNumShapes = 5;
+constexpr Shape kShapes[kNumShapes] = {{128, 256, 1, 1, 4.0f, 1.9f, 2.65f, 2.65f, 1.4f},
+                                       {64, 128, 1, 2, 4.0f, 0.85f, 0.94f, 1.52f, 1.25f},
+                                       {32, 128, 1, 2, 4.0f, 0.65f, 0.75f, 1.30f, 1.5f},
+                                       {32, 64, 4, 1, 6.0f, 0.72f, 1.15f, 1.20f, 1.2f},
+                                       {64, 128, 2, 1, 6.0f, 1.04f, 1.45f, 1.55f, 1.25f}};
 constexpr int kMaxKSplit = 8;
 constexpr int kMinSplitChunks = 2;
 
-// expected time of a launch of w workgroups of n chunks each; a groupwise store's chunk takes about
-// 1.5 times as long (its vector work between the matrix passes)
+// expected time of a launch of w workgroups of n chunks each
 float launch_us(const Shape& h, long w, int n, bool store) {
   const long slots = long(kNumCu) * h.per_cu;
-  auto chunk = [&](long u) {            // chunk time with u workgroups on the chip
+  auto step = [&](long u) {             // step time with u workgroups on the chip
     return u <= kNumCu ? h.t_one + (h.t_cu - h.t_one) * float(u) / kNumCu
                        : h.t_cu + (h.t_full - h.t_cu) * float(u - kNumCu) / float(slots - kNumCu);
   };
   const long rounds = w / slots, rest = w % slots;
-  return kFixedUs + (store ? 1.5f : 1.0f) * float(n) * (float(rounds) * h.t_full + (rest ? chunk(rest) : 0.0f));
+  const int steps = (n + h.kw - 1) / h.kw;
+  return h.fixed + (store ? h.store : 1.0f) * float(steps) * (float(rounds) * h.t_full + (rest ? step(rest) : 0.0f));
 }
 
 template <int MODE, bool SH>
@@ -540,9 +613,11 @@ hipError_t launch_mode(const PfI8Args& a, int shape, hipStream_t s) {
   const int rows = MODE == MM_GATEUP ? h.tn / 2 : h.tn;
   const int gx = (a.N + rows - 1) / rows, gy = (a.T + h.tm - 1) / h.tm;
   const dim3 grid(uint32_t(gx) * uint32_t(gy) * uint32_t(a.ks));
-  if (shape == 0) hipLaunchKernelGGL((pf_i8_kernel<MODE, 4, 4, 2, 2, SH>), grid, dim3(512), 0, s, a, gx, gy);
-  else if (shape == 1) hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 2, 2, 2, SH>), grid, dim3(256), 0, s, a, gx, gy);
-  else hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 1, 2, 1, SH>), grid, dim3(128), 0, s, a, gx, gy);
+  if (shape == 0) hipLaunchKernelGGL((pf_i8_kernel<MODE, 4, 4, 2, 1, 2, SH>), grid, dim3(512), 0, s, a, gx, gy);
+  else if (shape == 1) hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 2, 2, 1, 2, SH>), grid, dim3(256), 0, s, a, gx, gy);
+  else if (shape == 2) hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 1, 2, 1, 1, SH>), grid, dim3(128), 0, s, a, gx, gy);
+  else if (shape == 3) hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 1, 1, 4, 1, SH>), grid, dim3(256), 0, s, a, gx, gy);
+  else hipLaunchKernelGGL((pf_i8_kernel<MODE, 2, 2, 2, 2, 2, SH>), grid, dim3(512), 0, s, a, gx, gy);
   return hipGetLastError();
 }
 
@@ -563,8 +638,8 @@ hipError_t launch_quant(const PfQuantArgs& a, int width, hipStream_t s) {
 
 // The launch of least expected time (launch_us). A split adds its partial sums, written here and
 // read by the consumer (about 4 TB/s). Large shapes move fewer bytes per product; small ones and
-// splits fill the chip when there are few tokens: at 8 tokens the 8B down projection takes 119 us
-// on 32 x 1 workgroups of shape 0 and 11 us on 32 x 8 of shape 2, at 2048 tokens 184 us on shape 0
+// splits fill the chip when there are few tokens: at 16 tokens the 8B down projection takes 44 us
+// on 32 workgroups of shape 2 and 10.6 on 64 x 4 of shape 3, at 2048 tokens 184 us on shape 0
 // and 242 on shape 1. Without splits the tokens may be cut in two launches, the first of whole
 // rounds of shape 0, so that the last round is not mostly empty (8B gate/up at 700 tokens: 384
 // tiles of shape 0 are one and a half rounds, 158 us, 144 us on shape 1; 512 tokens in one round of
@@ -581,7 +656,7 @@ PfI8Plan plan_pf_i8(MfmaMode mode, const PfI8Args& a) {
   };
   PfI8Plan best{0, 1, 0, 0};
   float best_us = 3e38f;
-  for (int i = 0; i < 3; ++i)
+  for (int i = 0; i < kNumShapes; ++i)
     for (int k = 1; k <= max_ks; ++k) {
       const float us = launch_us(kShapes[i], tiles(i, a.T) * k, (chunks + k - 1) / k, store) +
                        (k > 1 ? float(k) * float(a.T) * float(a.N) * 4.0f * 2.0f / 4e6f : 0.0f);
@@ -592,7 +667,7 @@ PfI8Plan plan_pf_i8(MfmaMode mode, const PfI8Args& a) {
     }
   for (int cut = kShapes[0].tm; cut < a.T; cut += kShapes[0].tm) {
     const float head = launch_us(kShapes[0], tiles(0, cut), chunks, store);
-    for (int i = 1; i < 3; ++i) {
+    for (int i = 1; i < kNumShapes; ++i) {
       const float us = head + launch_us(kShapes[i], tiles(i, a.T - cut), chunks, store);
       if (us < 0.95f * best_us) {
         best_us = us;
@@ -614,7 +689,7 @@ hipError_t launch_part(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t 
     return hipErrorInvalidValue;
   }
   if (a.T < 1 || a.K < 0 || a.ldx % kKC != 0 || a.ldx < a.K || a.ks < 1 ||
-      shape < 0 || shape > 2 || size_t(a.T) * 4 * a.ldx >= size_t(kOOB) ||
+      shape < 0 || shape >= kNumShapes || size_t(a.T) * 4 * a.ldx >= size_t(kOOB) ||
       size_t(a.T) * 4 * std::max(a.ldy, a.N) >= size_t(kOOB) ||
       (a.ks > 1 && (mode == MM_GATEUP || !a.part || size_t(a.ks) * a.T * a.N > a.part_floats)))
     return hipErrorInvalidValue;

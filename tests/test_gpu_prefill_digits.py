@@ -59,6 +59,20 @@ def test_cut_launch(shared, d, f, T):
     assert _rel(case.run(), case.oracle()) < REL
 
 
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("d,f,T", [(384, 640, 20),        # three chunks for four groups
+                                   (640, 12800, 20),      # 32 x 64 tiles, one row tile of tokens
+                                   (1152, 12800, 33),     # nine chunks; a second, nearly empty token tile
+                                   (1152, 13056, 120)])   # 64 x 128 tiles, nine chunks over two groups
+def test_chunk_groups(shared, d, f, T):
+    """Tiles whose chunks are dealt to groups of waves (short prompts, and up to one workgroup per CU):
+    chunk counts that are no multiple of the groups, and fewer chunks than groups."""
+    print(f"case digits groups shared={shared} d={d} f={f} T={T}", flush=True)
+    sh = synth.tiny_shape(d=d, hq=4, hkv=2, dh=64, f=f)
+    case = PrefillCase(sh, synth.raw_mask(sh, 4, p_f=0.6, block=16), T, 3, shared=shared)
+    assert _rel(case.run(), case.oracle()) < REL
+
+
 def test_number_range():
     """Rows of zeros, of tiny and of large values, and rows with one value far above the rest: each
     token has its own scale, so a token's result does not depend on its neighbours, and its error
