@@ -104,12 +104,14 @@ enum MfmaMode { MM_QKV = 0, MM_RESID = 1, MM_GATEUP = 2, MM_LMHEAD = 3 };
 // A projection read from the groupwise shared store instead of a panel: INT8 rows [store_rows][ld]
 // with one BF16 scale per row and 128 columns; plan row n is store row rows[n] (identity when
 // rows is null), plan columns 16 p .. 16 p + 15 are store columns cols[p] .. cols[p] + 15
-// (identity when cols is null). Gate/up use w / gs for the gate and w2 / gs2 for the up matrix.
+// (identity when cols is null); whole: plan columns 128 g .. 128 g + 127 are one store group for every
+// g. Gate/up use w / gs for the gate and w2 / gs2 for the up matrix.
 struct StoreView {
   const int8_t* w; const int8_t* w2;
   const uint16_t* gs; const uint16_t* gs2;
   int ld, store_rows;
   const int* rows; const int* cols;
+  bool whole;
 };
 
 struct MfmaArgs {

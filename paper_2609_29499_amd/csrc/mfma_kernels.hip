@@ -18,11 +18,15 @@
 // applies scale, inverse RMS, residual / SwiGLU, and writes the next operand.
 //
 // Groupwise store (shared-store plans). The weights come from the store through the plan's row
-// map (QKV, gate/up) or 16-column piece map (O, down, staged in LDS), and a lane's 16 bytes lie in
-// one piece, hence in one group of 128 columns: it loads the group's BF16 scale with them and
-// forms w = q * s in float32, exact (7 + 8 significant bits), then splits it into BF16 hi and lo
-// parts (exact as well: the lo part keeps at most 7 bits). Both parts meet the hi/lo activation
-// columns, so one step costs four MFMAs instead of two and no per-row scale remains.
+// map (QKV, gate/up) or 16-column piece map (O, down, staged in LDS). Where each 128 plan columns are
+// one store group (no column map, or one that keeps whole groups) the bytes are widened as a panel's,
+// a group's two steps are summed by themselves and join the total with the group's scale. Operands
+// are swapped there, weights in the B operand, so that a lane's outputs belong to the one row whose
+// scale it loads. Otherwise (single heads of 64, channel blocks of 16) a lane's 16 bytes still lie in
+// one group: it forms w = q * s in float32, exact (7 + 8 significant bits), splits it into BF16 hi and
+// lo parts (exact as well: the lo part keeps at most 7 bits), and a step costs four MFMAs and three
+// times the vector work. The joined form is bound by the weight stream like the panels', the split one by
+// its vector work (8B gate/up at batch 4 28.8 us split, 21.9 joined).
 #include "device_common.hpp"
 #include "kernels.hpp"
 
@@ -112,7 +116,8 @@ struct EpiOps {
 // tile boundary at the same flattened step and the cross-wave reduction lines up. The load
 // stream runs across tile boundaries: the first steps of the next tile are in flight while the
 // current tile is reduced and stored.
-template <int MODE, int WAVES, int RT, bool SH>
+// SH: 0 panels, 1 groupwise store with split products, 2 groupwise store with whole groups
+template <int MODE, int WAVES, int RT, int SH>
 __global__ __launch_bounds__(WAVES * kWave) void mfma_gemv_kernel(MfmaArgs a) {
   constexpr int kPF = kStepsPerBatch / RT;             // steps per load batch (two batches in flight)
   constexpr bool BF = (MODE == MM_LMHEAD);
@@ -230,8 +235,14 @@ __global__ __launch_bounds__(WAVES * kWave) void mfma_gemv_kernel(MfmaArgs a) {
           const bool okr = ok && srow[rt] >= 0 && k < K;
           const int scol = okr ? (has_cols ? cmap_s[k >> 4] : k) : 0;
           const uint32_t wo = okr ? uint32_t(srow[rt]) * row_bytes + uint32_t(scol) : kOOB;
-          const uint32_t so = okr ? (uint32_t(srow[rt]) * sgroups + uint32_t(scol) / 128u) * 2u : kOOB;
-          if constexpr (GU) {
+          // (whole groups: one scale for the group's two steps)
+          const bool oks = okr && (SH == 1 || u % 2 == 0);
+          const uint32_t so = oks ? (uint32_t(srow[rt]) * sgroups + uint32_t(scol) / 128u) * 2u : kOOB;
+          if constexpr (GU && RT > 1) {
+            f[u].a[rt] = buf_load16_stream(rt >= RT / 2 ? rw2 : rw, wo);
+            if (SH == 1 || u % 2 == 0)
+              f[u].gs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rt >= RT / 2 ? rg2 : rg1, int(so), 0, 0);
+          } else if constexpr (GU) {
             // gate and up rows of one wave come from two store matrices: a resource must be
             // wave-uniform, so each lane loads from both with the other offset out of range
             // (no traffic) and keeps the union
@@ -239,11 +250,12 @@ __global__ __launch_bounds__(WAVES * kWave) void mfma_gemv_kernel(MfmaArgs a) {
             const int4 g4 = buf_load16_stream(rw, up ? kOOB : wo);
             const int4 u4 = buf_load16_stream(rw2, up ? wo : kOOB);
             f[u].a[rt] = make_int4(g4.x | u4.x, g4.y | u4.y, g4.z | u4.z, g4.w | u4.w);
-            f[u].gs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rg1, int(up ? kOOB : so), 0, 0) |
-                          __builtin_amdgcn_raw_buffer_load_b16(rg2, int(up ? so : kOOB), 0, 0);
+            if (SH == 1 || u % 2 == 0)
+              f[u].gs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rg1, int(up ? kOOB : so), 0, 0) |
+                            __builtin_amdgcn_raw_buffer_load_b16(rg2, int(up ? so : kOOB), 0, 0);
           } else {
             f[u].a[rt] = buf_load16_stream(rw, wo);
-            f[u].gs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rg1, int(so), 0, 0);
+            if (SH == 1 || u % 2 == 0) f[u].gs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rg1, int(so), 0, 0);
           }
         } else {
           const int row = lane_row(tile, rt);
@@ -280,7 +292,9 @@ __global__ __launch_bounds__(WAVES * kWave) void mfma_gemv_kernel(MfmaArgs a) {
       float v = 0.0f;
 #pragma unroll
       for (int w = 0; w < WAVES; ++w) v += red[w][ri][l];
-      tile_s[16 * (ri >> 2) + 4 * (l >> 4) + (ri & 3)][l & 15] = v;
+      const int m = 4 * (l >> 4) + (ri & 3), n = l & 15;  // output row and column of the MFMA
+      if constexpr (SH == 2) tile_s[16 * (ri >> 2) + n][m] = v;
+      else tile_s[16 * (ri >> 2) + m][n] = v;
     }
     __syncthreads();
     const int b = e_b;
@@ -312,6 +326,28 @@ __global__ __launch_bounds__(WAVES * kWave) void mfma_gemv_kernel(MfmaArgs a) {
   auto process = [&](const Frag<RT> (&f)[kPF], int g) {
     if (g >= total) return;
     const int i = g / spw, jb = g - i * spw;
+    if constexpr (SH == 2) {
+      static_assert(kPF % 2 == 0, "a group's two steps lie in one load batch");
+#pragma unroll
+      for (int u = 0; u < kPF; u += 2) {
+        if (wave * spw + jb + u >= n_steps) break;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          f32x4 g0{0.0f, 0.0f, 0.0f, 0.0f}, g1{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const Frag<RT>& w = f[u + h];
+            g0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w.x0),
+                                                         widen_i8(uint32_t(w.a[rt].x), uint32_t(w.a[rt].y)), g0, 0, 0, 0);
+            g1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w.x1),
+                                                         widen_i8(uint32_t(w.a[rt].z), uint32_t(w.a[rt].w)), g1, 0, 0, 0);
+          }
+          const float sc = bf16_to_f32(uint16_t(f[u].gs[rt]));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc0[rt][e] = fmaf(g0[e] + g1[e], sc, acc0[rt][e]);
+        }
+      }
+    } else
 #pragma unroll
     for (int u = 0; u < kPF; ++u) {
       if (wave * spw + jb + u >= n_steps) break;
@@ -320,7 +356,7 @@ __global__ __launch_bounds__(WAVES * kWave) void mfma_gemv_kernel(MfmaArgs a) {
         if (BF) {
           acc0[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[u].a[rt]),
                                                              __builtin_bit_cast(bf16x8, f[u].x0), acc0[rt], 0, 0, 0);
-        } else if constexpr (SH) {
+        } else if constexpr (SH == 1) {
           const float sc = bf16_to_f32(uint16_t(f[u].gs[rt]));
           bf16x8 h0, l0, h1, l1;
           widen_scaled(uint32_t(f[u].a[rt].x), uint32_t(f[u].a[rt].y), sc, h0, l0);
@@ -386,7 +422,7 @@ __global__ __launch_bounds__(kBlock) void mfma_prep_kernel(const float* __restri
   if ((threadIdx.x & 15) == 0 && i < D) ssq[size_t(b) * n_tiles + (i >> 4)] = ss;
 }
 
-template <int MODE, int WAVES, int RT, bool SH>
+template <int MODE, int WAVES, int RT, int SH>
 hipError_t launch_mm(const MfmaArgs& a, hipStream_t s) {
   const int rpt = (MODE == MM_GATEUP) ? 8 * RT : 16 * RT;
   const int tiles = (a.N + rpt - 1) / rpt;
@@ -411,15 +447,19 @@ hipError_t launch_mm_mode(const MfmaArgs& a, hipStream_t s) {
   const int rows = (MODE == MM_GATEUP) ? 2 * a.N : a.N;
   const bool two = rows >= (MODE == MM_RESID ? kMmTwoTileResidRows : kMmTwoTileRows);
   if constexpr (MODE != MM_LMHEAD) {
-    // (the store's widened weights weigh more than the operand: no four-tile form, and one tile on
-    // eight waves: 8B QKV at batch 4 13.5 us, on four 13.8; O 11.4 and 11.8)
-    if (a.sv.gs) return two ? launch_mm<MODE, 4, 2, true>(a, s) : launch_mm<MODE, 8, 1, true>(a, s);
+    // (no four-tile form for the store, and one tile on eight waves also for residual projections: 8B
+    // O at batch 4 7.2 us, on four waves 9.1)
+    if (a.sv.gs && (!a.sv.cols || a.sv.whole))
+      return two ? launch_mm<MODE, 4, 2, 2>(a, s) : launch_mm<MODE, 8, 1, 2>(a, s);
+  }
+  if constexpr (MODE == MM_RESID) {
+    if (a.sv.gs) return two ? launch_mm<MODE, 4, 2, 1>(a, s) : launch_mm<MODE, 8, 1, 1>(a, s);
   }
   if (MODE == MM_GATEUP && rows >= kMmFourTileRows && a.B >= kMmFourTileBatch)
-    return launch_mm<MODE, 4, 4, false>(a, s);
-  if (two) return launch_mm<MODE, 4, 2, false>(a, s);
-  if (MODE == MM_RESID) return launch_mm<MODE, 4, 1, false>(a, s);
-  return launch_mm<MODE, 8, 1, false>(a, s);
+    return launch_mm<MODE, 4, 4, 0>(a, s);
+  if (two) return launch_mm<MODE, 4, 2, 0>(a, s);
+  if (MODE == MM_RESID) return launch_mm<MODE, 4, 1, 0>(a, s);
+  return launch_mm<MODE, 8, 1, 0>(a, s);
 }
 
 }  // namespace
@@ -430,6 +470,7 @@ hipError_t launch_mfma_gemv(MfmaMode mode, const MfmaArgs& a, hipStream_t s) {
     // column groups, a column map only for piece-aligned K, no LM head
     if (mode == MM_LMHEAD || a.B < 1 || a.B > 8 || a.K < 0 || a.K % 16 != 0 || a.ldx % 64 != 0 ||
         a.ldx < a.K || a.sv.ld % 128 != 0 || a.sv.store_rows < 1 ||
+        ((!a.sv.cols || a.sv.whole) && a.K % 128 != 0) || (mode != MM_RESID && a.sv.cols && !a.sv.whole) ||
         (mode == MM_GATEUP && (!a.sv.w2 || !a.sv.gs2)))
       return hipErrorInvalidValue;
     if (size_t((a.K + 15) / 16) * 4 > 64 * 1024) return hipErrorInvalidValue;

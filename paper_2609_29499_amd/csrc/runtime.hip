@@ -406,7 +406,7 @@ tasp::StoreView store_view(const tasp_plan_s* p, int l, int which) {
       break;
     case 1:
       v.w = Q.o; v.gs = Q.s_o; v.ld = d.n_q_heads * d.head_dim; v.store_rows = d.d_model;
-      v.cols = Q.o_cols;
+      v.cols = Q.o_cols; v.whole = p->layers[l].m_q * d.head_dim == 128 * p->layers[l].o_chunks;
       break;
     case 3:
       v.w = Q.g; v.w2 = Q.u; v.gs = Q.s_g; v.gs2 = Q.s_u; v.ld = d.d_model; v.store_rows = d.d_ffn;
@@ -414,6 +414,7 @@ tasp::StoreView store_view(const tasp_plan_s* p, int l, int which) {
       break;
     default:
       v.w = Q.d; v.gs = Q.s_d; v.ld = d.d_ffn; v.store_rows = d.d_model; v.cols = Q.down_cols;
+      v.whole = p->layers[l].c == 128 * p->layers[l].d_chunks;
       break;
   }
   return v;

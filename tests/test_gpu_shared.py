@@ -246,6 +246,20 @@ def test_batched_decode(batch, pos):
     _check(Case(sh, synth.raw_mask(sh, 40 + batch, block=16), batch, pos, shared=True))
 
 
+@pytest.mark.parametrize("d,dh,f,block,B", [(512, 128, 1536, 128, 3),    # whole store groups everywhere
+                                            (512, 64, 1536, 128, 8),     # down whole, O by single heads
+                                            (512, 128, 1536, 16, 2),     # O whole, down by blocks of 16
+                                            (256, 128, 6400, 128, 5),    # two row tiles per wave, gate/up
+                                            (8192, 128, 256, 128, 2),    # and residual projections
+                                            (8192, 64, 256, 16, 4)])
+def test_batched_decode_group_forms(d, dh, f, block, B):
+    """Projections whose columns keep whole store groups (sums per group, then the scale) and those
+    that do not (scaled weights in two parts), one and two row tiles per wave."""
+    _flush(f"case shared batched groups d={d} dh={dh} f={f} block={block} B={B}")
+    sh = synth.tiny_shape(d=d, hq=8, hkv=4, dh=dh, f=f)
+    _check(Case(sh, synth.raw_mask(sh, 60 + B, p_q=0.6, p_f=0.6, block=block), B, 41, shared=True))
+
+
 def test_batched_decode_head_dim_128_and_empty_modules():
     _flush("case shared batched decode dh128 / empty modules")
     sh = synth.tiny_shape(d=512, hq=8, hkv=2, dh=128, f=1024, layers=1)
