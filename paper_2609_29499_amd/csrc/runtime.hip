@@ -186,7 +186,7 @@ void scratch_layout(Layout& Y, const tasp_model_desc* d, Take&& take, size_t& of
   Y.xo = take(batched ? size_t(16) * Y.ld_xo * 2 : 0);
   Y.xh = take(batched ? size_t(16) * Y.ld_xh * 2 : 0);
   Y.ssq = take(batched ? size_t(B) * (D / 16) * 4 : 0);
-  // prefill of up to P tokens: hi/lo operand planes, q planes, q/k/v, residuals, RMS partials
+  // prefill of up to P tokens: digit operands (or the LM head's hi/lo planes), q planes, q/k/v, residuals, RMS partials
   const size_t P = size_t(d->max_prefill);
   Y.ld_xw = round_up128(std::max(Hq * dh, F));
   Y.pxd = take(2 * P * Y.ld_xd * 2);
@@ -684,8 +684,8 @@ tasp_status prefill_head(tasp_plan p, const float* r, int T, float* out, hipStre
   return run_kernel(tm, 5, s, [&] { return tasp::launch_pf_head(a, s); });
 }
 
-// every projection on the INT8 matrix cores over digit operands. The normed inputs (QKV, gate/up) have their digits in pxd; the O and down inputs are written to pxw
-// in float32 and turned into digits there.
+// every projection on the INT8 matrix cores over digit operands. The normed inputs (QKV, gate/up) have
+// their digits in pxd; the O and down inputs are written to pxw in float32 and turned into digits there.
 tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0, float* out,
                          hipStream_t s, Timer* tm, bool last_only) {
   const tasp_model_desc& d = p->desc;
