@@ -60,8 +60,14 @@ constexpr int kXcds = 8;
 constexpr int kNumCu = 256;
 constexpr int kGroupM = 4;              // token tiles walked together by one XCD's workgroups
 
-// s_waitcnt: no vector memory operation outstanding, the other counters not waited on
-__device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
+// No vector memory or LDS operation of this wave outstanding, and none moved across by the compiler:
+// its loads into a stage have landed and its reads of one are done. The builtin wait and barrier alone
+// order neither: the compiler may sink the last reads' wait, with the products that need it, past them.
+__device__ __forceinline__ void stage_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(7 << 4);                   // vmcnt(0) lgkmcnt(0)
+  asm volatile("" ::: "memory");
+}
 
 // LDS slot of 16-byte piece p of row `row` (rows of kKC bytes): any 8 consecutive rows read at one
 // piece meet distinct banks
@@ -290,16 +296,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
       }
     }
   };
-  // chunk kc sits in stage kc % 2: wait for this wave's loads of it, meet the other waves (their
-  // loads of it have landed, and all of them are done with the other stage), load the next chunk
-  // into the other stage, multiply
+  // chunk kc sits in stage kc % 2: wait for this wave's loads of it and its reads of the other stage,
+  // meet the other waves that share the stages (one wave's group has none), load the next chunk into
+  // the other stage, multiply
   auto step = [&](int kc, const Stage& cur, Stage& nxt, const Scales& sv, Scales& sn) {
-    if constexpr (KW > 1 && NW == 1) {
-      __builtin_amdgcn_s_waitcnt(0);                    // (and its reads of the other stage are done)
-      asm volatile("" ::: "memory");
-    } else {
-      wait_vm0();
+    stage_done();
+    if constexpr (NW > 1) {
       __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
     }
     const int wc = store_chunk(kc + 1, entry);
     entry = list_entry(kc + 2);
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
     step(kc, st0, st1, sc0, sc1);
     if (kc + 1 < nkw) step(kc + 1, st1, st0, sc1, sc0);
   }
-  wait_vm0();
+  stage_done();
   __syncthreads();                                      // every wave is done with the stages
   // Token scales, and (KW > 1) the groups' sums: group kw adds up outputs EC kw .. + EC - 1 of every
   // lane and row tile, the others leave theirs in LDS (32 KiB per digit, two in st0, one in st1).
