@@ -307,13 +307,17 @@ __global__ __launch_bounds__(kBlock) void pf_attn_kernel(PfAttnArgs a) {
       for (int i = 0; i < 4; ++i) oo[d][i] = buf_load4f_device(rp, other + uint32_t(((d * 4 + i) * kWave + lane) * 4));
     const float mm = fmaxf(m_run, m_o);
     const float ws = __builtin_amdgcn_exp2f(m_run - mm), wo = __builtin_amdgcn_exp2f(m_o - mm);
-    const float lsum = l_run * ws + l_o * wo;
+    // chunk 0's share first, whichever chunk finished last: the two products of a contracted sum are
+    // not rounded alike, and the outputs do not depend on which workgroup comes second
+    const bool first = ch == 0;
+    auto sum = [&](float m, float wm, float p, float wp) { return fmaf(first ? m : p, first ? wm : wp, (first ? p : m) * (first ? wp : wm)); };
+    const float lsum = sum(l_run, ws, l_o, wo);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float s_i = lane_read(ws, 4 * c + i), o_i = lane_read(wo, 4 * c + i);
       inv[i] = 1.0f / lane_read(lsum, 4 * c + i);
 #pragma unroll
-      for (int d = 0; d < NDT; ++d) o[d][i] = o[d][i] * s_i + oo[d][i] * o_i;
+      for (int d = 0; d < NDT; ++d) o[d][i] = sum(o[d][i], s_i, oo[d][i], o_i);
     }
   } else {
 #pragma unroll

@@ -75,6 +75,18 @@ def test_prefill_repeat_bit_exact(T, pos0):
     assert_parity(first, case.oracle(), what="prefill repeat")
 
 
+@pytest.mark.parametrize("dh,T,pos0", [(128, 512, 0), (64, 330, 100)])
+def test_prefill_split_attention_repeats_bit_exact(dh, T, pos0):
+    """Many query blocks served by two workgroups each, either of which may finish last and combine the
+    two records: all of 16 repeated prefills give the same bits."""
+    _flush(f"case prefill split attention repeat dh={dh} T={T} pos0={pos0}")
+    sh = synth.tiny_shape(d=512, hq=32, hkv=8, dh=dh, f=256)
+    case = PrefillCase(sh, synth.all_kept_mask(sh), T, pos0)
+    first = case.run()
+    for _ in range(15):
+        assert np.array_equal(case.run(), first)
+
+
 @pytest.mark.parametrize("T,pos0", [(1, 0), (77, 0), (77, 128), (130, 5), (200, 300)])
 def test_prefill_ragged_and_offset(T, pos0):
     """Token counts that are not tile multiples, and prompts continuing a prior cache."""
