@@ -159,23 +159,24 @@ hipError_t launch_pf_prep(const float* x, int D, int T, const uint16_t* gamma, u
 int pf_ssq_block();
 
 // Projections on the INT8 matrix cores. The operand x holds one row of 4 ldx bytes per
-// token: three planes of ldx signed base-256 digits (high to low), then the token's
-// float32 scale. MM_QKV: y = product; MM_RESID: y = resid + product; MM_GATEUP: y = silu(gate) *
+// token: three planes of ldx signed base-256 digits (high to low), or, for a token whose scale has its
+// sign bit set, two planes of ldx BF16 (hi, lo). MM_QKV: y = product; MM_RESID: y = resid + product; MM_GATEUP: y = silu(gate) *
 // up. With ks > 1 (not MM_GATEUP) split z writes its product to part [z][T][N] instead.
 struct PfI8Args {
   const int8_t* w; uint32_t w2_off;   // panel rows [N][ld] (gate/up: gate rows; up at w2_off bytes)
   const float* scale; const float* scale2;
   int N, K, ld;
-  const uint8_t* x; int ldx;          // ldx % 128 == 0; digits zero to the next multiple of 128
+  const uint8_t* x; int ldx;          // ldx % 128 == 0; rows zero to the next multiple of 128
+  const float* tok;                   // [T] scales of the tokens
   const float* resid;                 // MM_RESID: [T][ldy]
   float* y; int ldy;
   int T, ks;
   float* part; size_t part_floats;
   // gs set: weights read from a groupwise store (w, w2_off, scale, ld unused). K is the operand's
   // width, a multiple of 128: with a column map, 128 times the store chunks of 128 columns that
-  // hold any retained column, listed by launch_pf_quant in x
+  // hold any retained column, listed in chunks
   StoreView sv;
-  const uint8_t* list;                // operand whose first row holds that list (null: x)
+  const int* chunks;
 };
 // How a projection is launched: tile shape and K splits (ks of the arguments is set from it), or
 // (cut > 0) the first `cut` tokens with `shape` and the others with `shape2`
@@ -184,8 +185,8 @@ struct PfI8Plan {
 };
 PfI8Plan plan_pf_i8(MfmaMode mode, const PfI8Args& a);
 hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a, const PfI8Plan& plan, hipStream_t s);
-// Digit rows o (PfI8Args::x layout, ldo bytes per digit) of the float32 rows x [T][ldx]. gamma:
-// the rows are x * gamma and the scale carries the inverse RMS of x. ks > 0: x is a residual
+// Operand rows o (PfI8Args::x layout, ldo bytes per digit) and scales tok of the float32 rows x
+// [T][ldx]. gamma: the rows are x * gamma and the scale carries the inverse RMS of x. ks > 0: x is a residual
 // [T][K], the row is x + sum of part [ks][T][K], stored to y [T][K] as well. Without gamma and ks
 // o may be x's own buffer (ldo == ldx).
 struct PfQuantArgs {
@@ -194,7 +195,9 @@ struct PfQuantArgs {
   const uint16_t* gamma; float inv_d, eps;
   const float* part; int ks; float* y;
   void* o; int ldo;
+  float* tok;
   const int* cols; int store_cols;    // column map (StoreView::cols) and width of the store's rows
+  int* chunks;                        // with a column map: the list of PfI8Args::chunks
 };
 hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s);
 // y = resid + sum of part [ks][T][N], rows of N floats

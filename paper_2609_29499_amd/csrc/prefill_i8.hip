@@ -6,16 +6,26 @@
 // written by pf_quant_kernel; the INT8 panel bytes are multiplied as they are, without widening.
 // Per (token, row) the three digit sums are exact integers and are joined in float32 in the
 // epilogue, so the only rounding before it is the digit grid: half a step of 2^-22 to 2^-23 of
-// the token's largest activation. Against the earlier operand pair (hi and lo BF16, about 2^-19
-// of each activation, on the BF16 matrix cores) the error of a random token is lower (rms 2^-22
+// the token's largest activation. Against an operand pair of hi and lo BF16 (about 2^-19 of each
+// activation, on the BF16 matrix cores) the error of a random token is lower (rms 2^-22
 // of the token's rms for a largest value of 4 to 5 rms), and the issued matrix work is three
 // INT8 passes (3 / 3.3 POP/s measured) instead of two BF16 passes (2 / 1.8 PFLOP/s measured).
 //
-// Row layout of an operand: ld bytes of d2, ld of d1, ld of d0, then the token's scale (float32,
-// times the inverse RMS for a normed input); ld is a multiple of the 128-byte chunk and the digits
-// from K to the end of its last chunk are zero, so panel bytes past the end of a row multiply
-// zeros. A row takes the 4 ld bytes of the float32 row it came from: the O and down inputs are
-// written in float32 and turned into digits in place.
+// Rows with outliers. Beside a value far above the rest one scale leaves the rest fewer bits than a
+// hi/lo pair does (with one value 1000 times the rms of 4096 others, an output that does not use that
+// column is off by 7e-5 of itself, with a pair by 2.4e-6). pf_quant_kernel compares the two errors of
+// every row (its comment has the rule) and carries a row for which digits are the worse form as a
+// pair. A tile with such rows multiplies its digit rows as always and then goes over K again with the
+// pairs, up to 64 of them gathered at a time, on the BF16 matrix cores with the panel bytes widened; a
+// tile of pairs alone skips the digits. The waves share the panel rows of that pass, not the tokens, so
+// that each widens its own only.
+//
+// Row layout of an operand: 4 ld bytes. Digits: ld bytes of d2, ld of d1, ld of d0. A pair: ld BF16 of
+// hi, ld of lo. ld is a multiple of the 128-byte chunk and either form is zero from K to the end of its
+// last chunk, so panel bytes past the end of a row multiply zeros. A row takes the 4 ld bytes of the
+// float32 row it came from: the O and down inputs are written in float32 and turned into their form in
+// place. The tokens' scales (float32, times the inverse RMS for a normed input) are an array of their
+// own, the sign bit telling a pair from digits.
 //
 // Tiling. Workgroups of TM tokens x TN rows (gate/up: TN / 2 channels, gate and up rows of a
 // channel in one wave); each wave holds its outputs, times three digits, in registers. K advances
@@ -29,7 +39,8 @@
 // accumulator (shifted between the two passes), converted and added to a float32 sum with the
 // scale, then d0 (five vector operations per output and chunk next to 48 matrix operations per 64
 // outputs and lane). Rows come through the plan's row map; a column-mapped operand is laid out in
-// the store's own chunks, those with any retained column, dropped columns zero. It replaced four
+// the store's own chunks, those with any retained column (listed by the operand's writer), dropped
+// columns zero. It replaced four
 // passes of hi/lo weights times hi/lo activations on the BF16 matrix cores: one 8B layer at 1000
 // tokens 998 -> 548 us.
 //
@@ -42,6 +53,7 @@
 // gate/up projection at 2048 tokens takes 960 instead of 1300 us; on the BF16 matrix cores with
 // hi/lo operands it took 2240 us.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -73,6 +85,16 @@ __device__ __forceinline__ void stage_done() {
 // piece meet distinct banks
 __device__ __forceinline__ int slot(int row, int p) { return p ^ (row & 7); }
 
+// eight INT8 values (exact in BF16) as a matrix operand, and an operand of the LDS
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+__device__ __forceinline__ uint32_t widen2(uint32_t w, int i) {
+  return __builtin_amdgcn_perm(__float_as_uint(float(int8_t(w >> (8 * i + 8)))), __float_as_uint(float(int8_t(w >> (8 * i)))),
+                               0x07060302u);
+}
+__device__ __forceinline__ bf16x8 widen8(const uint2& w) {
+  return __builtin_bit_cast(bf16x8, make_int4(int(widen2(w.x, 0)), int(widen2(w.x, 2)), int(widen2(w.y, 0)), int(widen2(w.y, 2))));
+}
+
 // the three digit sums of one output, joined in float32
 __device__ __forceinline__ float join(int s2, int s1, int s0) {
   return fmaf(float(s2), 65536.0f, fmaf(float(s1), 256.0f, float(s0)));
@@ -80,7 +102,9 @@ __device__ __forceinline__ float join(int s2, int s1, int s0) {
 
 // Workgroup id -> (n tile, m tile, split). Ids go round-robin over the XCDs; each XCD takes a
 // contiguous run of an order that walks kGroupM token tiles together, so that the workgroups an
-// XCD holds at one time share digit and panel rows in its L2.
+// XCD holds at one time share digit and panel rows in its L2. The token tile moves on by one in every
+// n tile: an XCD's shader engines take its workgroups in turn, and without the shift all tiles of the
+// same tokens, the slow ones if these have outlier rows, fell to one engine.
 __device__ __forceinline__ void tile_of(int id, int total, int gx, int gy, int& bx, int& by, int& bz) {
   const int x = id % kXcds, j = id / kXcds;
   const int o = x * (total / kXcds) + min(x, total % kXcds) + j;
@@ -89,8 +113,8 @@ __device__ __forceinline__ void tile_of(int id, int total, int gx, int gy, int& 
   const int grp = rem / (kGroupM * gx);
   const int gm = min(kGroupM, gy - grp * kGroupM);
   const int in = rem - grp * (kGroupM * gx);
-  by = grp * kGroupM + in % gm;
   bx = in / gm;
+  by = grp * kGroupM + (in + bx) % gm;
 }
 
 // NT tiles of 32 tokens x 32 rows per wave; WGM x WGN waves; WAVES: per SIMD; SH: groupwise store.
@@ -133,6 +157,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
 
   const uint32_t xrow = 4u * uint32_t(a.ldx);           // bytes of an operand row
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(a.x, uint32_t(T) * xrow);
+  // the tile's token scales: one per thread for the epilogue, and all of them in every wave for their
+  // signs (first of all loads, so that waiting for them does not wait for the chunks)
+  const __amdgpu_buffer_rsrc_t rt = make_rsrc(a.tok, uint32_t(T) * 4u);
+  auto token_scale = [&](int t) {                       // (zero past the tile and past the last token)
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rt, int(t < TM && m0 + t < T ? 4u * uint32_t(m0 + t) : kOOB), 0, 0));
+  };
+  const float tscale = token_scale(tid);
+  const float tsign[2] = {token_scale(lane), TM > 64 ? token_scale(lane + 64) : 0.0f};
   const uint32_t ldw = SH ? uint32_t(a.sv.ld) : uint32_t(a.ld);
   const uint32_t w_bytes = (SH ? uint32_t(a.sv.store_rows) : uint32_t(N)) * ldw;
   const __amdgpu_buffer_rsrc_t rw = make_rsrc(SH ? a.sv.w : a.w, !SH && GU ? a.w2_off + w_bytes : w_bytes);
@@ -160,10 +192,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   // Chunks past the last reload it (into a stage that is not read again), so that every step
   // issues alike. A row of a per-row panel may end inside its last chunk: the bytes loaded past it
   // are the next row's, or of the sections behind the panels, and meet zero digits. Store rows are
-  // whole chunks; with a column map the operand's chunk kc is the kc-th store chunk with any
-  // retained column, listed behind the first token's scale.
+  // whole chunks; with a column map the operand's chunk kc is store chunk a.chunks[kc].
   const bool mapped = SH && a.sv.cols != nullptr;
-  const __amdgpu_buffer_rsrc_t rl = make_rsrc((a.list ? a.list : a.x) + 3 * size_t(a.ldx) + 16, mapped ? uint32_t(nk_all) * 4u : 0u);
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc(a.chunks, mapped ? uint32_t(nk_all) * 4u : 0u);
   auto clamp_chunk = [&](int kc) { return kc0 + max(min(kw + KW * kc, nk - 1), 0); };
   auto list_entry = [&](int kc) {                       // loaded one step before it is used
     return mapped ? __builtin_amdgcn_raw_buffer_load_b32(rl, 4 * clamp_chunk(kc), 0, 0) : 0u;
@@ -171,16 +202,19 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   auto store_chunk = [&](int kc, uint32_t entry) {
     return mapped ? int(__builtin_amdgcn_readfirstlane(int(entry))) : clamp_chunk(kc);
   };
-  auto issue = [&](int kc, int wc, Stage& S) {
-    const int k0 = clamp_chunk(kc) * kKC, wk = SH ? wc * kKC : k0;
-#pragma unroll
-    for (int j = 0; j < APER; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S[kw * SBYTES + (wave + NW * j) * 1024]), 16, int(abase[j]), k0, 0, 0);
+  auto issue_panel = [&](int wk, Stage& S) {
 #pragma unroll
     for (int j = 0; j < BPER; ++j) {
       const __amdgpu_buffer_rsrc_t rj = SH && up_load(j) ? rw2 : rw;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rj, static_cast<void*>(&S[kw * SBYTES + SA + (wave + NW * j) * 1024]), 16, int(bbase[j]), wk, 0, 0);
     }
+  };
+  auto issue = [&](int kc, int wc, Stage& S) {
+    const int k0 = clamp_chunk(kc) * kKC;
+#pragma unroll
+    for (int j = 0; j < APER; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S[kw * SBYTES + (wave + NW * j) * 1024]), 16, int(abase[j]), k0, 0, 0);
+    issue_panel(SH ? wc * kKC : k0, S);
   };
 
   // panel rows of the lane's outputs, and (groupwise store) the byte offsets of their scales
@@ -214,12 +248,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
     return v;
   };
 
-  // the token scales go first, so that waiting for them does not wait for the chunks
-  float tscale = 0.0f;
-  if (tid < TM) {
-    const uint32_t off = uint32_t(m0 + tid) * xrow + 3u * uint32_t(a.ldx);
-    tscale = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, int(m0 + tid < T ? off : kOOB), 0, 0));
-  }
   const int first = store_chunk(0, list_entry(0));
   uint32_t entry = list_entry(1);
   Scales sc0 = load_scales(first), sc1{};
@@ -228,7 +256,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   // per-row panels: the digit sums over all of K; groupwise store: the scaled float32 sum, and the
   // digit sums of one chunk (one scale group) at a time
   i32x16 acc[SH ? 1 : 3][SH ? 1 : NT];
-  f32x16 facc[SH ? NT : 1];
+  f32x16 facc[NT];
 #pragma unroll
   for (int d = 0; d < (SH ? 1 : 3); ++d)
 #pragma unroll
@@ -236,7 +264,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[d][j][e] = 0;
 #pragma unroll
-  for (int j = 0; j < (SH ? NT : 1); ++j)
+  for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int e = 0; e < 16; ++e) facc[j][e] = 0.0f;
 
@@ -299,12 +327,15 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   // chunk kc sits in stage kc % 2: wait for this wave's loads of it and its reads of the other stage,
   // meet the other waves that share the stages (one wave's group has none), load the next chunk into
   // the other stage, multiply
-  auto step = [&](int kc, const Stage& cur, Stage& nxt, const Scales& sv, Scales& sn) {
+  auto stage_ready = [&] {
     stage_done();
     if constexpr (NW > 1) {
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     }
+  };
+  auto step = [&](int kc, const Stage& cur, Stage& nxt, const Scales& sv, Scales& sn) {
+    stage_ready();
     const int wc = store_chunk(kc + 1, entry);
     entry = list_entry(kc + 2);
     if constexpr (SH) sn = load_scales(wc);
@@ -312,20 +343,23 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
     if (KW == 1 || kw + KW * kc < nk) compute(cur, sv);
   };
   const int nkw = (nk + KW - 1) / KW;                   // steps, the same for every group
-  for (int kc = 0; kc < nkw; kc += 2) {
-    step(kc, st0, st1, sc0, sc1);
-    if (kc + 1 < nkw) step(kc + 1, st1, st0, sc1, sc0);
+  // the tile's tokens whose rows are pairs
+  const unsigned long long pair_tok[2] = {__ballot(__float_as_int(tsign[0]) < 0), __ballot(__float_as_int(tsign[1]) < 0)};
+  const int n_pair = __popcll(pair_tok[0]) + __popcll(pair_tok[1]);
+  if (n_pair < min(TM, T - m0)) {
+    for (int kc = 0; kc < nkw; kc += 2) {
+      step(kc, st0, st1, sc0, sc1);
+      if (kc + 1 < nkw) step(kc + 1, st1, st0, sc1, sc0);
+    }
   }
   stage_done();
   __syncthreads();                                      // every wave is done with the stages
-  // Token scales, and (KW > 1) the groups' sums: group kw adds up outputs EC kw .. + EC - 1 of every
-  // lane and row tile, the others leave theirs in LDS (32 KiB per digit, two in st0, one in st1).
+  // (KW > 1) the groups' sums: group kw adds up outputs EC kw .. + EC - 1 of every lane and row tile, the
+  // others leave theirs in LDS (32 KiB per digit, two in st0, one in st1).
   constexpr int ND = SH ? 1 : 3, QG = 4 / KW;           // digits, groups of four outputs per wave group
   constexpr int QS = KW == 2 ? 2 : 4;                   // groups of four a wave leaves (KW 4: its own unused)
   constexpr size_t kSumBytes = KW > 1 ? size_t(KW) * NW * NT * QS * kWave * 16 : 0;   // of one digit
   static_assert((ND > 1 ? 2 : 1) * kSumBytes <= sizeof(st0) && kSumBytes + TM * 4 <= sizeof(st1), "the sums fit the stages");
-  float* ts = reinterpret_cast<float*>(reinterpret_cast<char*>(&st1) + kSumBytes);
-  if (tid < TM) ts[tid] = tscale;
   auto sums = [&](int d, int k, int nt, int g) -> i32x4* {
     char* base = d < 2 ? reinterpret_cast<char*>(&st0) + size_t(d) * kSumBytes : reinterpret_cast<char*>(&st1);
     return reinterpret_cast<i32x4*>(base) + (((k * NW + wave) * NT + nt) * QS + g % QS) * kWave + lane;
@@ -342,9 +376,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           if (g / QG != kw) *sums(d, kw, nt, g) = i32x4{bits(d, nt, 4 * g), bits(d, nt, 4 * g + 1), bits(d, nt, 4 * g + 2), bits(d, nt, 4 * g + 3)};
-  }
-  __syncthreads();
-  if constexpr (KW > 1) {
+    __syncthreads();
 #pragma unroll
     for (int d = 0; d < ND; ++d)
 #pragma unroll
@@ -373,6 +405,164 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
           }
         }
   }
+  if constexpr (!SH) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int e = 0; e < EC; ++e) facc[nt][e] = join(acc[0][nt][e], acc[1][nt][e], acc[2][nt][e]);
+  }
+  auto token = [&](int e) { return wm * 32 + 8 * ((EC * kw + e) >> 2) + 4 * hi + (e & 3); };
+
+  // ---- the pairs, MB of them at a time: MB x TN outputs of which a wave has MB x 32 PT (its group's
+  // chunks), 64 columns of K a step. These are 128 bytes of hi and of lo of a token, where the digit planes
+  // were, and one half of the panel rows' chunk.
+  if (n_pair > 0) {
+    // (the lane anew, so that nothing derived from it here is kept in registers through the loop above)
+    int plane_id = lane;
+    asm volatile("" : "+v"(plane_id));
+    const int lane = plane_id, r = lane & 31, hi = lane >> 5;
+    constexpr int MB = TM == 32 ? 32 : 64, MT = MB / 32, PT = NT / WGM, PPER = 2 * MB / RPL / NW;
+    static_assert(PT * WGM == NT && PPER * RPL * NW == 2 * MB, "even share of the rows and loads");
+    static_assert(MB * 256 + TM * 4 <= SA && KW * MB * TN * 4 <= int(sizeof(st0)), "list and sums fit the stages");
+    int* const list = reinterpret_cast<int*>(reinterpret_cast<char*>(&st0) + MB * 256);   // tokens that are pairs
+    float* const out = reinterpret_cast<float*>(&st0);                                    // [KW][MB][TN] sums
+    // the wave's 32 tokens: which are pairs, and the pairs before them
+    const uint32_t own = uint32_t(pair_tok[wm >> 1] >> (32 * (wm & 1)));
+    const int before = (wm >> 1 ? __popcll(pair_tok[0]) : 0) + (wm & 1 ? __popc(uint32_t(pair_tok[wm >> 1])) : 0);
+    // byte offset of the scales of the lane's rows in the wave's row tiles; gate or up of a row tile
+    uint32_t pgroup[SH ? PT : 1];
+    auto pair_row = [&](int j) { return (wave * PT + j) * 32; };       // its first row in the tile
+    if constexpr (SH) {
+#pragma unroll
+      for (int j = 0; j < PT; ++j) {
+        const int lr = pair_row(j) + r, row = panel_row(GU ? n0 + HN * (lr / (2 * HN)) + lr % HN : n0 + lr);
+        pgroup[j] = row >= 0 ? uint32_t(row) * sgroups * 2u : kOOB;
+      }
+    }
+    auto pair_scales = [&](int wc) {
+      Scales v{};
+      if constexpr (SH) {
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+          const __amdgpu_buffer_rsrc_t rn = GU && pair_row(j) % (2 * HN) >= HN ? rg2 : rg;
+          v.s[j] = __builtin_amdgcn_raw_buffer_load_b16(rn, int(pgroup[j]), 2 * wc, 0);
+        }
+      }
+      return v;
+    };
+#pragma unroll 1
+    for (int p0 = 0; p0 < n_pair; p0 += MB) {
+      __syncthreads();                                  // what LDS held has been read
+      if (tid < TM && __float_as_int(tscale) < 0)
+        list[(tid >> 6 ? __popcll(pair_tok[0]) : 0) + __popcll(pair_tok[tid >> 6 ? 1 : 0] & ((1ull << lane) - 1))] = tid;
+      __syncthreads();
+      uint32_t pbase[PPER];
+#pragma unroll
+      for (int j = 0; j < PPER; ++j) {
+        const int i = wave + NW * j, plane = i / (MB / RPL), lr = (i % (MB / RPL)) * RPL + lane / LPR;
+        const int t = p0 + lr < n_pair ? m0 + list[p0 + lr] : 0;
+        pbase[j] = p0 + lr < n_pair ? uint32_t(t) * xrow + uint32_t(plane) * 2u * uint32_t(a.ldx) + 16u * slot(lr, lane % LPR) : kOOB;
+      }
+      auto issue_pairs = [&](int kc, int half, int wc, Stage& S) {
+        const int k0 = clamp_chunk(kc) * kKC;
+#pragma unroll
+        for (int j = 0; j < PPER; ++j)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, static_cast<void*>(&S[kw * SBYTES + (wave + NW * j) * 1024]), 16,
+                                                   int(pbase[j]), 2 * k0 + kKC * half, 0, 0);
+        issue_panel(SH ? wc * kKC : k0, S);
+      };
+      f32x16 sum[MT][PT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < PT; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) sum[m][j][e] = 0.0f;
+      // (lane (r, hi) of a product holds k = 8 hi .. + 7 of its 16 columns, on either side)
+      auto multiply = [&](const Stage& S, int half, const Scales& sv) {
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+          f32x16 u[MT];
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) u[m][e] = SH ? 0.0f : sum[m][j][e];
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) {
+            const bf16x8 wf = widen8(*reinterpret_cast<const uint2*>(
+                &S[kw * SBYTES + SA + (pair_row(j) + r) * kKC + 16 * slot(r, 4 * half + ks) + 8 * hi]));
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+              if (m > 0 && p0 + 32 * m >= n_pair) continue;
+#pragma unroll
+              for (int d = 0; d < 2; ++d) {
+                const i32x4 x = *reinterpret_cast<const i32x4*>(
+                    &S[kw * SBYTES + (d * MB + m * 32 + r) * kKC + 16 * slot(r, 2 * ks + hi)]);
+                u[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), wf, u[m], 0, 0, 0);
+              }
+            }
+          }
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            if constexpr (SH) {
+              const float s = bf16_to_f32(uint16_t(sv.s[j]));
+#pragma unroll
+              for (int e = 0; e < 16; ++e) sum[m][j][e] = fmaf(u[m][e], s, sum[m][j][e]);
+            } else {
+              sum[m][j] = u[m];
+            }
+          }
+        }
+      };
+      // a chunk's halves in st0 and st1, the next 64 columns in flight while one is multiplied
+      int wc = store_chunk(0, list_entry(0));
+      Scales sv = pair_scales(wc);
+      issue_pairs(0, 0, wc, st0);
+#pragma unroll 1
+      for (int kc = 0; kc < nkw; ++kc) {
+        const bool mine = KW == 1 || kw + KW * kc < nk;
+        const int wn1 = store_chunk(kc + 1, list_entry(kc + 1));
+        const Scales sn = pair_scales(wn1);
+        stage_ready();
+        issue_pairs(kc, 1, wc, st1);
+        if (mine) multiply(st0, 0, sv);
+        stage_ready();
+        issue_pairs(kc + 1, 0, wn1, st0);
+        if (mine) multiply(st1, 1, sv);
+        wc = wn1;
+        sv = sn;
+      }
+      stage_done();
+      __syncthreads();                                  // every wave is done with the stages
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < PT; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            out[(kw * MB + 32 * m + 8 * (e >> 2) + 4 * hi + (e & 3)) * TN + pair_row(j) + r] = sum[m][j][e];
+      __syncthreads();
+      int first = 4 * hi;
+      asm volatile("" : "+v"(first));                   // (or the masks of all outputs are kept over the loop)
+#pragma unroll
+      for (int e = 0; e < EC; ++e) {
+        const uint32_t bit = 1u << (8 * ((EC * kw + e) >> 2) + first + (e & 3));
+        const int i = before + __popc(own & (bit - 1)) - p0;
+        if (!(own & bit) || i < 0 || i >= MB) continue;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          float f = out[i * TN + (wn * NT + nt) * 32 + r];
+#pragma unroll
+          for (int k = 1; k < KW; ++k) f += out[(k * MB + i) * TN + (wn * NT + nt) * 32 + r];
+          facc[nt][e] = f;
+        }
+      }
+    }
+  }
+  float* const ts = reinterpret_cast<float*>(&st1);
+  if constexpr (KW > 1) __syncthreads();                // the sums have been read
+  if (tid < TM) ts[tid] = fabsf(tscale);
+  __syncthreads();
 
   // ---- epilogue: lane (r, hi) holds tokens 8 g + 4 hi + i of the token tile for row r
   // (KW > 1: outputs EC kw .. of each row tile)
@@ -392,9 +582,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   const __amdgpu_buffer_rsrc_t rr = make_rsrc(resid ? a.resid : nullptr, resid ? out_bytes : 0u);
   auto value = [&](int nt, int e, float tsc) {
     if constexpr (SH) return facc[nt][e] * tsc;
-    else return join(acc[0][nt][e], acc[1][nt][e], acc[2][nt][e]) * tsc * sc[nt];
+    else return facc[nt][e] * tsc * sc[nt];
   };
-  auto token = [&](int e) { return wm * 32 + 8 * ((EC * kw + e) >> 2) + 4 * hi + (e & 3); };
   auto offset = [&](int nt, int e) {
     const int t = m0 + token(e);
     return t < T && col[nt] < N ? (uint32_t(t) * ldo + uint32_t(col[nt])) * 4u : kOOB;
@@ -427,20 +616,33 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   }
 }
 
-// Float32 rows -> digit rows. One workgroup per token; thread i holds elements 4 (i + THREADS j).
+// Float32 rows -> operand rows. One workgroup per token; thread i holds elements 4 (i + THREADS j).
 // With a gain: the operand is x * gamma and the token's scale carries the inverse RMS of x. With
 // K splits (part): x = resid + the splits' sum (in split order), which is also stored to y. The
-// row is read in full before any digit is written, so source and destination may be one buffer.
+// row is read in full before any of it is written, so source and destination may be one buffer.
 // The scale is the largest power of two 2^-e that keeps q = rint(v 2^e) within three digits
 // (|q| <= 0x7f7f7f); a row with a non-finite value gets a NaN scale, a zero row digits of zero.
+//
+// Digits or pair. In steps of the digit grid a digit's error has the variance 1 / 12, whatever the
+// element; that of a pair, for a value f, is about f^2 2^-32 0.308 / 12 (the lo part's rounding, averaged
+// over where lo falls in its binade and f in its own). Elements from an eighth of the row's largest up
+// are held better by digits. Over the nonzero others the sums are compared: where the sum of f^2 -
+// 2^32 / 0.308 is negative, digits would lose against a pair on outputs of these columns alone, and the
+// row becomes a pair. Random rows stay digits (the rms of those elements is at least 1.6 times the
+// threshold on 1000 Gaussian rows of 64, 2.4 times from 512 on, 1.13 times on 3200 rows of SwiGLU products of
+// 150 to 28672); a row with one value of more than about 35 to 70 times the rms of the others does not. Nor
+// does a row too small for a normal scale, whose digits would lack bits. (The comparison costs 0.5 to 1 us
+// a launch: 8B layer at 512 tokens 243 -> 248 us. With one outlier token it takes 299 us, with one in nine
+// tokens 305, in every token 306; the kernel on hi/lo operands throughout took 390.)
 // MAPPED (groupwise store, no gain, no splits): x holds the retained columns in pieces of 16, piece p
 // being store columns cols[p] .. + 15; the operand holds the store's chunks of 128 columns with any
-// retained piece, in order, dropped pieces zero, and their list is written behind token 0's scale.
+// retained piece, in order, dropped pieces zero; the chunks' list is written to a.chunks.
 // Bound by its 4 to 8 bytes read and 3 written per element.
+constexpr float kPairSquare = 1.39e10f; // 2^32 / 0.308
 constexpr int kMaxPieces = 2560;        // store pieces of the widest input (40960 columns)
 template <int THREADS, int NV, bool MAPPED>
 __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
-  __shared__ float red[2][THREADS / kWave];
+  __shared__ float red[3][THREADS / kWave];
   const int tid = threadIdx.x, t = blockIdx.x, K = a.K, ld = a.ldo;
   int kz = (K + kKC - 1) / kKC * kKC;                    // digits written: K and its zero padding
   uint8_t* row = reinterpret_cast<uint8_t*>(a.o) + size_t(t) * 4 * ld;
@@ -532,16 +734,47 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
   const bool finite = mb < 0x7f800000u;
   const float big = __uint_as_float(mb);
   // big 2^e in [2^22, 2^23), one less where the digits would not hold it; e <= 126 keeps the scale
-  // a normal number (smaller rows lose digits below 2^-126)
+  // a normal number
   int e = 22 - ((int(mb >> 23)) - 127);
-  if (mb < 0x00800000u || e > 126) e = 126;
+  const bool tiny = mb < 0x00800000u || e > 126;
+  if (tiny) e = 126;
   if (ldexpf(big, e) > 8355711.0f) --e;
-  const float up = ldexpf(1.0f, e > 127 ? 127 : e);
+  float up = ldexpf(1.0f, e > 127 ? 127 : e);
+  // the comparison's sum, over the workgroup
+  const float small = big * up * 0.125f;
+  float more = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const float f[4] = {v[j].x * up, v[j].y * up, v[j].z * up, v[j].w * up};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      more += fabsf(f[i]) < small && f[i] != 0.0f ? fmaf(f[i], f[i], -kPairSquare) : 0.0f;
+  }
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) more += __shfl_xor(more, o, kWave);
+  if ((tid & 63) == 0) red[2][w] = more;
+  __syncthreads();
+  more = 0.0f;
+#pragma unroll
+  for (int i = 0; i < THREADS / kWave; ++i) more += red[2][i];
+  const bool pair = finite && (more < 0.0f || (tiny && mb != 0));
+  asm volatile("" : "+v"(up));                          // (or the products above stay in registers)
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int k = 4 * (tid + THREADS * j);
     if (k >= kz) continue;
     const float f[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+    if (pair) {
+      uint32_t h[4], l[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        h[i] = f32_to_bf16(f[i]);
+        l[i] = f32_to_bf16(f[i] - bf16_to_f32(uint16_t(h[i])));
+      }
+      *reinterpret_cast<uint2*>(row + 2 * k) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+      *reinterpret_cast<uint2*>(row + 2 * (size_t(ld) + k)) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+      continue;
+    }
     uint32_t d2 = 0, d1 = 0, d0 = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -557,13 +790,13 @@ __global__ __launch_bounds__(THREADS) void pf_quant_kernel(PfQuantArgs a) {
     *reinterpret_cast<uint32_t*>(row + 2 * size_t(ld) + k) = d0;
   }
   if (tid == 0) {
-    float s = ldexpf(1.0f, -e);
+    float s = pair ? 1.0f : ldexpf(1.0f, -e);
     if (a.gamma) s *= rsqrtf(ss * a.inv_d + a.eps);
-    *reinterpret_cast<float*>(row + 3 * size_t(ld)) = finite ? s : __uint_as_float(0x7fc00000u);
+    a.tok[t] = !finite ? __uint_as_float(0x7fc00000u) : pair ? -s : s;
   }
   if constexpr (MAPPED) {
     if (t == 0)
-      for (int i = tid; i < kz / kKC; i += THREADS) reinterpret_cast<int*>(row + 3 * size_t(ld) + 16)[i] = chunk[i];
+      for (int i = tid; i < kz / kKC; i += THREADS) a.chunks[i] = chunk[i];
   }
 }
 
@@ -692,7 +925,7 @@ hipError_t launch_part(MfmaMode mode, const PfI8Args& a, int shape, hipStream_t 
   } else if (a.K > a.ld || a.ld % 16 != 0) {
     return hipErrorInvalidValue;
   }
-  if (a.T < 1 || a.K < 0 || a.ldx % kKC != 0 || a.ldx < a.K || a.ks < 1 ||
+  if (a.T < 1 || a.K < 0 || a.ldx % kKC != 0 || a.ldx < a.K || a.ks < 1 || !a.tok || (a.sv.cols && !a.chunks) ||
       shape < 0 || shape >= kNumShapes || size_t(a.T) * 4 * a.ldx >= size_t(kOOB) ||
       size_t(a.T) * 4 * std::max(a.ldy, a.N) >= size_t(kOOB) ||
       (a.ks > 1 && (mode == MM_GATEUP || !a.part || size_t(a.ks) * a.T * a.N > a.part_floats)))
@@ -716,8 +949,7 @@ hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a0, const PfI8Plan& plan,
   a.T = plan.cut;
   const hipError_t e = launch_part(mode, a, plan.shape, s);
   if (e != hipSuccess) return e;
-  // the other tokens (a column-mapped operand's chunk list stays behind the first token's scale)
-  a.list = a0.list ? a0.list : a0.x;
+  a.tok = a0.tok + plan.cut;
   a.x = a0.x + size_t(plan.cut) * 4 * a.ldx;
   if (a.resid) a.resid += size_t(plan.cut) * a.ldy;
   a.y += size_t(plan.cut) * a.ldy;
@@ -726,11 +958,11 @@ hipError_t launch_pf_i8(MfmaMode mode, const PfI8Args& a0, const PfI8Plan& plan,
 }
 
 hipError_t launch_pf_quant(const PfQuantArgs& a, hipStream_t s) {
-  if (a.T < 1 || a.K < 0 || a.ldo % kKC != 0 || a.ldo < a.K || a.ldx % 4 != 0 || ((a.gamma || a.ks) && a.K % 4 != 0))
+  if (a.T < 1 || a.K < 0 || !a.tok || a.ldo % kKC != 0 || a.ldo < a.K || a.ldx % 4 != 0 || ((a.gamma || a.ks) && a.K % 4 != 0))
     return hipErrorInvalidValue;
   if (a.cols) {
     // the operand's width is at most the store's (one register array holds the row)
-    if (a.gamma || a.ks || a.K % 16 != 0 || a.store_cols % kKC != 0 || a.store_cols < a.K ||
+    if (!a.chunks || a.gamma || a.ks || a.K % 16 != 0 || a.store_cols % kKC != 0 || a.store_cols < a.K ||
         a.store_cols > 16 * kMaxPieces || a.ldo < a.store_cols)
       return hipErrorInvalidValue;
     return a.store_cols <= 4 * 256 * 7 ? launch_quant<256, true>(a, a.store_cols, s)

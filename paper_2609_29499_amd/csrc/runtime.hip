@@ -144,6 +144,7 @@ struct Layout {
   size_t final_norm, lm_head, rope_cos, rope_sin;
   size_t r_mid, r_io0, r_io1, qkv_buf, o_buf, h_buf, part, acnt;
   size_t xd, xo, xh, ssq;            // batched path: hi/lo operands and sums of squares
+  size_t ptok, pchunks;              // scales and chunk list of the projection operand in use
   size_t pxd, pxw, pq, pqkv, pr_mid, pr_io0, pr_io1, pssq;   // prefill scratch
   size_t ppart, ppart_floats;                                // prefill K-split partials and
                                                              // split attention records
@@ -186,9 +187,11 @@ void scratch_layout(Layout& Y, const tasp_model_desc* d, Take&& take, size_t& of
   Y.xo = take(batched ? size_t(16) * Y.ld_xo * 2 : 0);
   Y.xh = take(batched ? size_t(16) * Y.ld_xh * 2 : 0);
   Y.ssq = take(batched ? size_t(B) * (D / 16) * 4 : 0);
-  // prefill of up to P tokens: digit operands (or the LM head's hi/lo planes), q planes, q/k/v, residuals, RMS partials
+  // prefill of up to P tokens: digit or pair operands (or the LM head's hi/lo planes), q planes, q/k/v, residuals, RMS partials
   const size_t P = size_t(d->max_prefill);
   Y.ld_xw = round_up128(std::max(Hq * dh, F));
+  Y.ptok = take(P * 4);
+  Y.pchunks = take(P ? size_t(Y.ld_xw) / 128 * 4 : 0);
   Y.pxd = take(2 * P * Y.ld_xd * 2);
   Y.pxw = take(2 * P * Y.ld_xw * 2);
   Y.pq = take(2 * size_t(Hq) * P * dh * 2);
@@ -346,6 +349,8 @@ struct tasp_plan_s {
   uint16_t *xd, *xo, *xh;            // batched path operands [16][ld_x*]
   float* ssq;                        // [max_batch][d_model / 16]
   int ld_xd, ld_xo, ld_xh;
+  float* ptok;                       // prefill: scales of the operand in use [max_prefill]
+  int* pchunks;                      // and its list of store chunks
   uint16_t *pxd, *pxw, *pq;          // prefill operands: [2][max_prefill][ld_xd | ld_xw], q planes
   float *pqkv, *pr_mid, *pr_io[2], *pssq;
   float* ppart;                      // prefill K-split partials, split attention records
@@ -376,6 +381,8 @@ void set_scratch(tasp_plan_s* p, const Layout& Y, char* ws) {
   p->xh = reinterpret_cast<uint16_t*>(at(Y.xh));
   p->ssq = reinterpret_cast<float*>(at(Y.ssq));
   p->ld_xd = Y.ld_xd; p->ld_xo = Y.ld_xo; p->ld_xh = Y.ld_xh;
+  p->ptok = reinterpret_cast<float*>(at(Y.ptok));
+  p->pchunks = reinterpret_cast<int*>(at(Y.pchunks));
   p->pxd = reinterpret_cast<uint16_t*>(at(Y.pxd));
   p->pxw = reinterpret_cast<uint16_t*>(at(Y.pxw));
   p->pq = reinterpret_cast<uint16_t*>(at(Y.pq));
@@ -684,8 +691,33 @@ tasp_status prefill_head(tasp_plan p, const float* r, int T, float* out, hipStre
   return run_kernel(tm, 5, s, [&] { return tasp::launch_pf_head(a, s); });
 }
 
-// every projection on the INT8 matrix cores over digit operands. The normed inputs (QKV, gate/up) have
-// their digits in pxd; the O and down inputs are written to pxw in float32 and turned into digits there.
+// The weights' side of a prefill projection of T tokens in layer l: kind 0 QKV, 2 O, 3 gate/up, 4 down
+// (the timed kernels' numbers).
+tasp::PfI8Args pf_projection(const tasp_plan_s* p, int l, int kind, int T) {
+  const LayerPlan& P = p->layers[l];
+  const int D = p->desc.d_model, kq = P.m_q * p->desc.head_dim;
+  tasp::PfI8Args a{};
+  a.T = T; a.part = p->ppart; a.part_floats = p->ppart_floats; a.tok = p->ptok; a.chunks = p->pchunks;
+  if (p->shared) a.sv = store_view(p, l, kind < 2 ? kind : kind == 2 ? 1 : kind);
+  switch (kind) {
+    case 0: a.w = P.qkv; a.scale = P.s_qkv; a.N = P.n_qkv; a.K = D; a.ld = D; break;
+    case 2: a.w = P.o; a.scale = P.s_o; a.N = D; a.K = p->shared ? 128 * P.o_chunks : kq; a.ld = P.ld_o; break;
+    case 3:
+      a.w = P.g; a.scale = P.s_g; a.scale2 = P.s_u; a.N = P.c; a.K = D; a.ld = D;
+      if (!p->shared) a.w2_off = uint32_t(reinterpret_cast<const char*>(P.u) - reinterpret_cast<const char*>(P.g));
+      break;
+    default: a.w = P.dn; a.scale = P.s_d; a.N = D; a.K = p->shared ? 128 * P.d_chunks : P.c; a.ld = P.ld_d; break;
+  }
+  return a;
+}
+tasp::MfmaMode pf_mode(int kind) {
+  return kind == 0 ? tasp::MM_QKV : kind == 3 ? tasp::MM_GATEUP : tasp::MM_RESID;
+}
+
+// every projection on the INT8 matrix cores over digit operands (rows with outliers: hi/lo BF16 pairs).
+// The normed inputs (QKV, gate/up) have theirs in pxd; the O and down inputs are written to pxw in
+// float32 and turned into operand rows there. One operand is in use at a time, so all share ptok and
+// pchunks.
 tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cache, int pos0, float* out,
                          hipStream_t s, Timer* tm, bool last_only) {
   const tasp_model_desc& d = p->desc;
@@ -694,24 +726,25 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
   const size_t layer_cache = size_t(cache->batch) * d.n_kv_heads * cache->max_seq * dh;
   float* wide = reinterpret_cast<float*>(p->pxw);
   tasp_status st;
-  auto gemm = [&](int kind, tasp::MfmaMode mode, tasp::PfI8Args& a) {
-    a.T = T; a.part = p->ppart; a.part_floats = p->ppart_floats;
+  auto gemm = [&](int kind, tasp::PfI8Args& a) {
+    const tasp::MfmaMode mode = pf_mode(kind);
     const tasp::PfI8Plan plan = tasp::plan_pf_i8(mode, a);
     a.ks = plan.ks;
     return run_kernel(tm, kind, s, [&] { return tasp::launch_pf_i8(mode, a, plan, s); });
   };
-  // digits of (r [+ the ks splits' sum, stored to y]) * gamma into pxd
+  // operand rows of (r [+ the ks splits' sum, stored to y]) * gamma into pxd
   auto quant_norm = [&](const float* r, const uint16_t* gamma, int ks, float* y) {
     tasp::PfQuantArgs a{};
     a.x = r; a.ldx = D; a.K = D; a.T = T; a.gamma = gamma; a.inv_d = 1.0f / float(D); a.eps = d.rms_eps;
     a.part = p->ppart; a.ks = ks > 1 ? ks : 0; a.y = y; a.o = p->pxd; a.ldo = p->ld_xd;
+    a.tok = p->ptok;
     return run_kernel(tm, 6, s, [&] { return tasp::launch_pf_quant(a, s); });
   };
   // a shared-store plan's columns go to their places in the store's chunks (cols)
   auto quant_wide = [&](int K, const tasp::StoreView& v) {
     tasp::PfQuantArgs a{};
     a.x = wide; a.ldx = p->ld_xw; a.K = K; a.T = T; a.o = wide; a.ldo = p->ld_xw;
-    a.cols = v.cols; a.store_cols = v.ld;
+    a.tok = p->ptok; a.cols = v.cols; a.store_cols = v.ld; a.chunks = p->pchunks;
     return run_kernel(tm, 6, s, [&] { return tasp::launch_pf_quant(a, s); });
   };
   if ((st = quant_norm(x, p->layers[0].an, 1, nullptr))) return st;
@@ -722,11 +755,9 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
     uint16_t* kc = static_cast<uint16_t*>(cache->k) + l * layer_cache;
     uint16_t* vc = static_cast<uint16_t*>(cache->v) + l * layer_cache;
     if (P.n_qkv > 0) {
-      tasp::PfI8Args a{};
-      a.w = P.qkv; a.scale = P.s_qkv; a.N = P.n_qkv; a.K = D; a.ld = D;
+      tasp::PfI8Args a = pf_projection(p, l, 0, T);
       a.x = reinterpret_cast<uint8_t*>(p->pxd); a.ldx = p->ld_xd; a.y = p->pqkv; a.ldy = p->ld_qkv;
-      if (p->shared) a.sv = store_view(p, l, 0);
-      if ((st = gemm(0, tasp::MM_QKV, a))) return st;
+      if ((st = gemm(0, a))) return st;
       tasp::PfRopeArgs r{};
       r.qkv = p->pqkv; r.ld_qkv = p->ld_qkv; r.ks = a.ks;
       if (a.ks > 1) {
@@ -746,36 +777,23 @@ tasp_status prefill_impl(tasp_plan p, const float* x, int T, tasp_kv_cache* cach
       t.part = p->ppart; t.part_floats = p->ppart_floats; t.cnt = p->pacnt; t.cnt_len = p->pacnt_len;
       if ((st = run_kernel(tm, 1, s, [&] { return tasp::launch_pf_attn(t, s); }))) return st;
     }
-    const tasp::StoreView vo = p->shared ? store_view(p, l, 1) : tasp::StoreView{};
-    const tasp::StoreView vd = p->shared ? store_view(p, l, 4) : tasp::StoreView{};
-    if ((st = quant_wide(P.m_q * dh, vo))) return st;
     {
-      tasp::PfI8Args a{};
-      a.w = P.o; a.scale = P.s_o; a.N = D; a.K = p->shared ? 128 * P.o_chunks : P.m_q * dh; a.ld = P.ld_o;
-      a.sv = vo;
+      tasp::PfI8Args a = pf_projection(p, l, 2, T);
+      if ((st = quant_wide(P.m_q * dh, a.sv))) return st;
       a.x = reinterpret_cast<uint8_t*>(p->pxw); a.ldx = p->ld_xw; a.resid = in; a.y = p->pr_mid; a.ldy = D;
-      if ((st = gemm(2, tasp::MM_RESID, a))) return st;
+      if ((st = gemm(2, a))) return st;
       if ((st = quant_norm(a.ks > 1 ? in : p->pr_mid, P.fn, a.ks, p->pr_mid))) return st;
     }
     if (P.c > 0) {
-      tasp::PfI8Args a{};
-      if (p->shared) {
-        a.sv = store_view(p, l, 3);
-      } else {
-        a.w = P.g;
-        a.w2_off = uint32_t(reinterpret_cast<const char*>(P.u) - reinterpret_cast<const char*>(P.g));
-      }
-      a.scale = P.s_g; a.scale2 = P.s_u; a.N = P.c; a.K = D; a.ld = D;
+      tasp::PfI8Args a = pf_projection(p, l, 3, T);
       a.x = reinterpret_cast<uint8_t*>(p->pxd); a.ldx = p->ld_xd; a.y = wide; a.ldy = p->ld_xw;
-      if ((st = gemm(3, tasp::MM_GATEUP, a))) return st;
+      if ((st = gemm(3, a))) return st;
     }
-    if ((st = quant_wide(P.c, vd))) return st;
     {
-      tasp::PfI8Args a{};
-      a.w = P.dn; a.scale = P.s_d; a.N = D; a.K = p->shared ? 128 * P.d_chunks : P.c; a.ld = P.ld_d;
-      a.sv = vd;
+      tasp::PfI8Args a = pf_projection(p, l, 4, T);
+      if ((st = quant_wide(P.c, a.sv))) return st;
       a.x = reinterpret_cast<uint8_t*>(p->pxw); a.ldx = p->ld_xw; a.resid = p->pr_mid; a.y = lo; a.ldy = D;
-      if ((st = gemm(4, tasp::MM_RESID, a))) return st;
+      if ((st = gemm(4, a))) return st;
       if (l + 1 < L) {
         if ((st = quant_norm(a.ks > 1 ? p->pr_mid : lo, p->layers[l + 1].an, a.ks, lo))) return st;
       } else if (a.ks > 1) {
@@ -927,6 +945,16 @@ tasp_status decode_impl(tasp_plan p, const float* x, tasp_kv_cache* cache, int32
 }
 
 }  // namespace
+
+namespace tasp {
+// How a prefill of T tokens launches a projection (kind as for pf_projection): out = tile shape, K
+// splits, and, where the tokens are cut in two launches, the first launch's tokens and the second's
+// shape. Not part of the C ABI: the tests ask here which path a case takes.
+void prefill_launch(const tasp_plan_s* p, int layer, int kind, int T, int* out) {
+  const PfI8Plan plan = plan_pf_i8(pf_mode(kind), pf_projection(p, layer, kind, T));
+  out[0] = plan.shape; out[1] = plan.ks; out[2] = plan.cut; out[3] = plan.shape2;
+}
+}  // namespace tasp
 
 // ------------------------------------------------------------------------------- C ABI
 // (every entry point below is declared extern "C" in tasp.h; helpers between them sit in

@@ -7,11 +7,14 @@ shows up as a non-finite output. The oracle receives the same prior rows and fin
 elsewhere (its zero-masked dropped heads do read their group's rows, with no effect)."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
 import synth
 from oracle import reference as ref
+from paper_2609_29499_amd import binding as B
 from paper_2609_29499_amd import session as S
 
 NAN_BF16 = np.uint16(0x7FC0)
@@ -117,6 +120,16 @@ class PrefillCase:
             self.plan.bind(self.cache)
         self.xd = torch.from_numpy(self.x).to(device)
         self.out = torch.full((T, sh.vocab if lm else sh.d_model), float("nan"), device=device)
+
+    def launch(self, kind, layer=0):
+        """How the library launches a projection of this prefill ("qkv", "o", "gateup", "down"): (tile
+        shape, K splits, tokens of the first of two launches or 0, shape of the second). Shapes: 0 128 x
+        256, 1 64 x 128, 2 32 x 128, 3 32 x 64 with four chunk groups, 4 64 x 128 with two."""
+        f = getattr(B.load(), "_ZN4tasp14prefill_launchEPK11tasp_plan_siiiPi")
+        f.argtypes, f.restype = [ctypes.c_void_p, *[ctypes.c_int] * 3, ctypes.POINTER(ctypes.c_int)], None
+        out = (ctypes.c_int * 4)()
+        f(self.plan.handle, layer, {"qkv": 0, "o": 2, "gateup": 3, "down": 4}[kind], self.T, out)
+        return tuple(out)
 
     def run(self):
         self.plan.prefill(self.xd, self.T, self.cache, self.pos0, self.out)

@@ -139,3 +139,83 @@ def test_groupwise_store_edges(what):
         f[:] = 0
     case = PrefillCase(sh, (q, kv, f), 520 if wide else 33, 0, shared=True)
     assert _rel(case.run(), case.oracle()) < REL
+
+
+def _outlier_case(shared, d, f, T, ratio, where, some):
+    """A layer without heads (no rounding of k and v between the input and the result) whose outputs do
+    not use the columns with the outliers. where "x": column 3 of the tokens in `some` is `ratio` times the
+    rms of the others, and no gate or up row reads it; "h": channel 5's up row is `ratio` times the
+    others', and the down projection does not read it. The scales make the layer's own contribution
+    larger than the residual, which float32 adds to it."""
+    sh = synth.tiny_shape(d=d, hq=2, hkv=1, dh=64, f=f)
+    layer = synth.layer_weights(sh, 0, quant="group" if shared else "row")
+
+    def scale(name, factor, rows=slice(None)):
+        w, s = layer[name]
+        s = s.copy()
+        s[rows] = synth.to_bf16_bits(synth.bf16_bits_to_f32(s[rows]) * np.float32(factor)) if shared else s[rows] * np.float32(factor)
+        layer[name] = (w, s)
+
+    def drop(name, column):
+        w = layer[name][0].copy()
+        w[:, column] = 0
+        layer[name] = (w, layer[name][1])
+
+    scale("wd", 64.0)
+    if where == "x":
+        # the RMS of a row with the outlier is ratio / sqrt(d)
+        up = 2.0 ** max(0, round(np.log2(ratio / np.sqrt(d))))
+        for n in ("wg", "wu"):
+            scale(n, up)
+            drop(n, 3)
+    else:
+        scale("wu", 2.0 ** round(np.log2(ratio)), slice(5, 6))
+        drop("wd", 5)
+    q, kv, ff = synth.all_kept_mask(sh)
+    q[:] = 0
+    case = PrefillCase(sh, (q, kv, ff), T, 0, store=[layer], shared=shared)
+    if where == "x":
+        x = case.x.copy()
+        x[some, 3] = ratio * np.sign(x[some, 3] + 0.5)
+        case.x, case.xd = x, torch.from_numpy(x).cuda()
+    return case
+
+
+OUTLIER_CASES = [   # store, widths, tokens, launches: every tile shape of both projections
+    (False, 512, 512, 5, dict(gateup=(2, 1, 0, 0), down=(2, 2, 0, 0))),
+    (False, 1024, 512, 5, dict(gateup=(3, 1, 0, 0))),
+    (False, 512, 12288, 33, dict(gateup=(1, 1, 0, 0))),
+    (False, 4096, 2048, 33, dict(down=(1, 8, 0, 0))),
+    (False, 1024, 1024, 700, dict(gateup=(4, 1, 0, 0))),
+    (False, 512, 6144, 330, dict(gateup=(0, 1, 0, 0))),
+    (False, 4096, 528, 1040, dict(down=(0, 1, 0, 0))),
+    (False, 1024, 4096, 1040, dict(gateup=(0, 1, 1024, 3))),
+    (True, 512, 512, 520, dict(down=(3, 1, 0, 0))),
+    (True, 512, 12288, 5, dict(gateup=(2, 1, 0, 0), down=(3, 8, 0, 0))),
+    (True, 512, 8192, 33, dict(gateup=(1, 1, 0, 0))),
+    (True, 1024, 8192, 130, dict(down=(4, 8, 0, 0))),
+    (True, 512, 16384, 200, dict(gateup=(0, 1, 0, 0))),
+    (True, 8192, 512, 1000, dict(down=(0, 1, 0, 0))),
+    (True, 8192, 2048, 1060, dict(down=(0, 1, 1024, 3)))]
+
+
+@pytest.mark.parametrize("shared,d,f,T,launches", OUTLIER_CASES)
+def test_outlier_rows(shared, d, f, T, launches):
+    """Rows with one value far above the others: what does not use that value is as exact as with hi/lo
+    BF16 operands. Such an operand is off by rms 2.4e-6 (2^-16 sqrt(0.308 / 12)) of its rms; the layer's
+    result takes that from gate, up and down, 2.4e-6 sqrt(3) with silu's slope up to 1.1, so 5e-6; four
+    times that is allowed (with digits alone: 7e-5 to 2e-3 at these ratios)."""
+    every = np.arange(T)
+    for where, ratio, some in (("x", 1000.0, every[every % 5 == 2]),       # digit and pair rows in a tile
+                               ("x", 3e5, every),                          # pair rows only
+                               ("h", 60.0, every),                         # about half of the rows
+                               ("h", 1e4, every)):
+        print(f"case outliers shared={shared} d={d} f={f} T={T} {where} {ratio}", flush=True)
+        case = _outlier_case(shared, d, f, T, ratio, where, some)
+        for kind, want in launches.items():
+            assert case.launch(kind) == want
+        # (the outlier's own column holds it in float32 beside the layer's result)
+        got, want = (np.delete(y - case.x, 3, axis=1) for y in (case.run(), case.oracle()))
+        rel = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+        print(f"  relative error: largest {rel.max():.2e}, median {np.median(rel):.2e}", flush=True)
+        assert rel.max() < 2e-5, (where, ratio, int(rel.argmax()))

@@ -36,13 +36,16 @@ def _kernels(tmp_path):
     return {n: i for n, i in out.items() if "pf_i8_kernel" in n}
 
 
-def test_every_barrier_follows_a_wait_for_lds_reads(tmp_path):
+def test_stage_barriers_follow_a_wait_for_lds_reads(tmp_path):
     kernels = _kernels(tmp_path)
     assert len(kernels) == 30          # three modes, five tile shapes, two stores
     for name, ins in kernels.items():
-        at = [i for i, t in enumerate(ins) if t.startswith("s_barrier")]
-        assert at, name
-        for i in at:
+        at = [i for i, t in enumerate(ins) if t.startswith("s_barrier")] + [len(ins)]
+        # the barriers behind which loads into LDS are issued
+        stage = [i for i, end in zip(at, at[1:])
+                 if any(t.startswith("buffer_load") and t.endswith(" lds") for t in ins[i:end])]
+        assert len(stage) >= 2 or "Li1ELi1ELi4E" in name, name     # (one wave's group shares its stages with no other)
+        for i in stage:
             # between the barrier and the wait before it: no LDS access, and the wait covers LDS
             j = next(j for j in range(i - 1, -1, -1) if ins[j].startswith("s_waitcnt"))
             assert "lgkmcnt(0)" in ins[j], f"{name}: {ins[j]} before a barrier"
