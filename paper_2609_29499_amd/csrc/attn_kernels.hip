@@ -48,8 +48,11 @@ constexpr int kMaxHeads = 8;
 constexpr int kNumCu = 256;
 constexpr int kMfmaChunk = 64;         // rows per split of the matrix-core kernel: a multiple of this
 // Contexts up to this many rows stay in one split: its four waves' extra tiles cost less than the
-// exchange of records (one tiny layer at 128 positions 19.2 -> 17.6 us, at 200 19.8 -> 18.8; 8B
-// layer at 128 positions 40.2 -> 38.9, at 200 and 256 the same; at 400 one split is 1.2 us slower).
+// exchange of records. Layer steps of a replayed graph, splits of 64 and 128 rows -> one: d_model 512
+// at 128 / 200 / 255 positions 20.3 -> 18.4, 20.6 -> 19.5, 20.6 -> 19.4 us (batch 8: 26.3 -> 24.3, 26.1 ->
+// 25.2, 26.8 -> 25.3); 8B 44.8 -> 43.5, 45.2 -> 45.1, 45.6 -> 45.0 (batch 8: 82.3 -> 81.3, the others the
+// same). Past 256 one split gains 0.3 to 1.1 us at batch 1 up to 350 positions and loses as much at batch
+// 8; at 400 it loses 0.9 us (8B, batch 1) to 2 us (batch 8).
 constexpr int kMfmaOneSplit = 256;
 constexpr int kMfmaTargetSplits = 32;  // split count beyond which its splits grow
 constexpr int kMfmaMaxSplit = 32;      // its merge handles up to this many splits
@@ -559,37 +562,33 @@ hipError_t launch_attn_decode(const AttnArgs& a, hipStream_t s) {
 }
 
 void attn_mfma_split(int total, int* chunk, int* n_split) {
-  // the smallest multiple of 64 rows that keeps the split count at 32 or fewer, and at least 128
-  // rows (two tiles per wave, the second's loads in flight during the first) once the context
-  // holds 256; the remainder joins the last split. At 2048 positions 16 splits of 128 rows
+  // one split up to kMfmaOneSplit rows; then the smallest multiple of 64 rows that keeps the split
+  // count at 32 or fewer, and at least 128 rows (two tiles per wave, the second's loads in flight
+  // during the first); the remainder joins the last split. At 2048 positions 16 splits of 128 rows
   // measured faster than 32 of 64 (fewer records to merge), at 4096 positions 32 of 128 faster
   // than 16 or 22 longer ones.
-  const int n64 = total / kMfmaChunk;
   if (total <= kMfmaOneSplit) {
     *chunk = (total + kMfmaChunk - 1) / kMfmaChunk * kMfmaChunk;
     *n_split = 1;
     return;
   }
-  int k = (n64 + kMfmaTargetSplits - 1) / kMfmaTargetSplits;
-  if (k < 2 && n64 >= 4) k = 2;
-  *chunk = kMfmaChunk * k;
+  const int n64 = total / kMfmaChunk;
+  *chunk = kMfmaChunk * std::max(2, (n64 + kMfmaTargetSplits - 1) / kMfmaTargetSplits);
   *n_split = std::max(1, total / *chunk);
 }
 void attn_mfma_split_batched(int total, int units, int* chunk, int* n_split) {
   // a batch: about one workgroup per CU over all (sequence, group slot) units. The cache rows
   // (total - 1; the new one is folded into the last split) are cut into splits of a multiple of
-  // 64 rows, at least 128 once the context holds 256, the last one shorter. At 8 sequences of
+  // 64 rows, at least 128, the last one shorter. At 8 sequences of
   // 8192 positions: 4 splits of 2048 rows.
   const int cached = total - 1;
-  const int n64 = total / kMfmaChunk;
   if (total <= kMfmaOneSplit || units >= kNumCu) {
     attn_mfma_split(total, chunk, n_split);
     return;
   }
   const int target = std::max(1, std::min(kNumCu / std::max(units, 1), kMfmaTargetSplits));
   int rows = (cached + target - 1) / target;
-  rows = (rows + kMfmaChunk - 1) / kMfmaChunk * kMfmaChunk;
-  if (rows < 2 * kMfmaChunk && n64 >= 4) rows = 2 * kMfmaChunk;
+  rows = std::max(2 * kMfmaChunk, (rows + kMfmaChunk - 1) / kMfmaChunk * kMfmaChunk);
   *chunk = rows;
   *n_split = std::max(1, (cached + rows - 1) / rows);
 }
