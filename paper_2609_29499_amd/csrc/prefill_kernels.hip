@@ -17,6 +17,7 @@
 
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "split_sums.hpp"
 
 namespace tasp {
 namespace {
