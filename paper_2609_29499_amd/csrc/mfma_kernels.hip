@@ -44,8 +44,11 @@ constexpr int kNumCu = 256;
 // 10.4 to 12.5). Residual projections have long rows in few tiles and take two from 8192 rows (4096 x
 // 8192 at batch 4: 13.9 -> 18.4 us with two), below that one tile on four waves (eight: 14.6). Gate/up
 // panels of at least 15360 rows (240 tiles of 64 rows: every CU but 16 busy) take four at batches of
-// 7 and 8 (8B at batch 8 23.6 -> 22.7 us, 70B 78.5 -> 73.9), where operand reads weigh most; smaller
-// batches are faster with two (8B at batch 2 21.1 -> 19.6 us, 70B at batch 4 70.3 -> 66.6).
+// 7 and 8, where operand reads weigh most (8B at batch 8 23.6 -> 22.7 us, 70B 78.5 -> 73.9), two below. The
+// layer's step with two -> four at batches 3 to 8, us: 8B 52.3 -> 53.2, 54.3 -> 54.9, 56.1 -> 56.5, 58.1 ->
+// 58.0, 59.9 -> 59.4, 62.3 -> 61.2; its dense plan 76.4 -> 78.1, 80.2 -> 80.9, the same, 87.0 -> 86.2, 90.1 ->
+// 88.6, 94.5 -> 91.9; 70B 135.3 -> 141.4, 140.5 -> 144.6, 146.2 -> 148.0, 152.0 -> 151.5, 157.6 -> 155.4,
+// 163.9 -> 159.4.
 constexpr int kMmTwoTileRows = 6144;
 constexpr int kMmTwoTileResidRows = 8192;
 constexpr int kMmFourTileRows = 15360;

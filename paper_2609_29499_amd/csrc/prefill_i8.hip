@@ -130,6 +130,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   constexpr int HN = 16 * NT;                           // gate/up: channels per wave
   constexpr int TM = 32 * WGM, TN = 32 * NT * WGN, NW = WGM * WGN;
   constexpr int EC = 16 / KW;                           // outputs per row tile and lane
+  constexpr int kUnrollK = KW > 1 ? 4 : 2;              // steps of 32 columns
   constexpr int RPL = 1024 / kKC, LPR = kKC / 16;       // rows per 1 KiB load, lanes per row
   constexpr int APER = 3 * TM / RPL / NW, BPER = TN / RPL / NW;
   static_assert(APER * RPL * NW == 3 * TM && BPER * RPL * NW == TN, "even share of the loads");
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   };
   auto compute = [&](const Stage& S, const Scales& sv) {
     if constexpr (!SH) {
-#pragma unroll (KW > 1 ? 4 : 2)
+#pragma unroll kUnrollK
       for (int ks = 0; ks < kKC / 32; ++ks) {
         i32x4 bf[NT];
 #pragma unroll
@@ -881,7 +882,11 @@ hipError_t launch_quant(const PfQuantArgs& a, int width, hipStream_t s) {
 // and 242 on shape 1. Without splits the tokens may be cut in two launches, the first of whole
 // rounds of shape 0, so that the last round is not mostly empty (8B gate/up at 700 tokens: 384
 // tiles of shape 0 are one and a half rounds, 158 us, 144 us on shape 1; 512 tokens in one round of
-// shape 0 and 188 on shape 1, 136 us).
+// shape 0 and 188 on shape 1, 136 us). A cut has to promise 5 % of the projection, which is about what
+// the model is off by: with any gain 8B layers of 780, 820, 1300 and 1800 tokens go from 384, 390, 648, 771 to
+// 399, 408, 662, 792 us, 70B ones of 700, 900 and 1700 from 1139, 1355, 2439 to 1161, 1384, 2512, against
+// 1700 tokens at 8B (751 -> 728) and 1300 and 1800 at 70B (1941 -> 1909, 2585 -> 2565); without cuts 1040
+// tokens take 588 instead of 530 us, and 1728 instead of 1505.
 PfI8Plan plan_pf_i8(MfmaMode mode, const PfI8Args& a) {
   const int chunks = (a.K + kKC - 1) / kKC;
   const bool store = a.sv.gs != nullptr;
