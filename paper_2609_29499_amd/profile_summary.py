@@ -64,8 +64,9 @@ def kind_of(name: str) -> str | None:
 
 
 def _named(kinds):
-    """Resolve resid_* into o_* / down_* by order: a residual GEMV right after gate/up is down;
-    a split-K reduction takes the name of the GEMM it follows."""
+    """Resolve resid_* into o_* / down_* by order: a residual GEMV right after gate/up is down
+    (operand preparation between them aside); a split-K reduction takes the name of the GEMM it
+    follows."""
     out, prev = [], None
     for k in kinds:
         if k and k.startswith("resid_"):
@@ -75,7 +76,7 @@ def _named(kinds):
             else:
                 k = ("down_" if prev and prev.startswith("gateup_") else "o_") + suffix
         out.append(k)
-        if k:
+        if k and k != "operand_prep":
             prev = k
     return out
 
