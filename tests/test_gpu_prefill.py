@@ -47,13 +47,17 @@ def test_tiny_layer_prefill(masked):
     _check_cache(case)
 
 
-def test_prefill_70b_width_split_k():
-    """Llama-3-70B width (8192, 64 / 8 heads, d_h 128) with a narrow FFN, 256 tokens after 64
-    prior positions: the 8192-row O and down panels and the QKV panel run as 256 tiles of 64
-    tokens with K split 4 ways (down: 1024 / 32 = 32 k chunks)."""
-    _flush("case prefill 70b width split k")
-    sh = synth.tiny_shape(d=8192, hq=64, hkv=8, dh=128, f=1024, theta=500000.0)
-    case = PrefillCase(sh, synth.raw_mask(sh, 12, p_q=0.7, p_kv=0.9), 256, 64)
+@pytest.mark.parametrize("T,launches", [(40, dict(qkv=(4, 4, 0, 0), o=(1, 6, 0, 0), down=(2, 2, 0, 0))),
+                                        (256, dict(qkv=(4, 1, 0, 0), o=(4, 1, 0, 0), down=(1, 1, 0, 0)))])
+def test_prefill_70b_width(T, launches):
+    """Llama-3-70B width (8192, 64 / 8 heads, d_h 128) with a narrow FFN, tokens after 64 prior
+    positions: at 40 the 8192-row O and down panels and the QKV panel split K 6, 2 and 4 ways, at
+    256 none does."""
+    _flush(f"case prefill 70b width T={T}")
+    sh = synth.tiny_shape(d=8192, hq=64, hkv=8, dh=128, f=2048, theta=500000.0)
+    case = PrefillCase(sh, synth.raw_mask(sh, 12, p_q=0.7, p_kv=0.9), T, 64)
+    for kind, want in launches.items():
+        assert case.launch(kind) == want
     got, want = case.run(), case.oracle()
     m, s = assert_parity(got, want, what="prefill 70b width")
     _flush(f"  max_rel={m:.2e} sum_rel={s:.2e}")
@@ -62,13 +66,14 @@ def test_prefill_70b_width_split_k():
 
 @pytest.mark.parametrize("T,pos0", [(128, 0), (330, 100)])
 def test_prefill_repeat_bit_exact(T, pos0):
-    """The QKV, O and down GEMMs of these prefills split K (2 to 4 splits per tile, summed in split
-    order by the reduction), and at 330 tokens after 100 prior positions the attention splits its
+    """The QKV and down projections of these prefills split K (2 and 4 ways, summed in split order by
+    whoever reads the sums next), and at 330 tokens after 100 prior positions the attention splits its
     longest query blocks over two workgroups (the second to finish combines the records, in an
     order-independent way): repeated prefills give the same bits."""
     _flush(f"case prefill repeat T={T} pos0={pos0}")
     sh = synth.TINY
     case = PrefillCase(sh, synth.tiny_mask(sh), T, pos0)
+    assert case.launch("qkv") == (2, 2, 0, 0) and case.launch("down") == (2, 4, 0, 0)
     first = case.run()
     for _ in range(3):
         assert np.array_equal(case.run(), first)

@@ -1,13 +1,17 @@
 """Prefill projections over digit operands (24-bit fixed point under one scale per token, three INT8
-passes): tile and split remainders of the three tile shapes, ragged K, and rows at the edges of the
-number range.
+passes): token, row and K remainders and K splits of the five tile shapes, from panels and from the
+groupwise store, cut launches, rows at the edges of the number range and rows with outliers. Every case
+states which launch it is meant for and checks that the library takes it.
 
-Tolerance: a digit operand is within 2^-23 of its token's largest activation (half a step of a
-power-of-two grid of at least 2^22 steps), so a product over K columns is within 2^-23 sqrt(K) times
-(largest / rms) of its 2-norm, under 1e-5 for K <= 8192 and a largest value of 8 rms. What exceeds
-that is the rounding of k and v to BF16: a value near a tie moves by one step (2^-8 of it), for a
-share of the entries of about the relative error before it over 2^-8. 2e-4 of the 2-norm covers one
-entry in a thousand moving. (Hi/lo BF16 operands on the same cases: up to 1e-4.)"""
+Tolerances. A digit is within half a step of its element, and a step is at most 2^-22 of the token's
+largest: an operand is off by rms 2^-22 / sqrt(12) (largest / rms), which is 3.4e-7 for a normed input
+(largest value 5 rms) and up to 1.8e-6 for a SwiGLU product (26 rms, in the worst place of its binade;
+mostly half of that). A layer without heads has no other rounding above 1e-7: REL_MLP = 4e-6 of the
+layer's own contribution, per token, is above the sum of the three and 20 times below what any digit
+plane left out would show (2^-14 / sqrt(12) (largest / rms), 9e-5 at least). With heads k and v are
+rounded to BF16, and a value near a tie moves by one step (2^-8 of it), for a share of the entries of
+about the relative error before it over 2^-8: REL = 2e-4 of the 2-norm covers one entry in a thousand
+moving. (Hi/lo BF16 operands on the same cases: up to 1e-4.)"""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +21,7 @@ from tests.gpu_case import PrefillCase
 
 pytestmark = pytest.mark.gpu
 REL = 2e-4
+REL_MLP = 4e-6
 
 
 def _rel(got, want):
@@ -27,56 +32,137 @@ def _case(sh, T, pos0=0, seed=5, p_f=0.6):
     return PrefillCase(sh, synth.raw_mask(sh, seed, p_f=p_f), T, pos0)
 
 
+def _takes(case, **launches):
+    """(tile shape, K splits, tokens of the first of two launches, shape of the second) per projection."""
+    for kind, want in launches.items():
+        assert case.launch(kind) == want, kind
+
+
+def _scale(layer, name, factor, rows=slice(None)):
+    w, s = layer[name]
+    s = s.copy()
+    s[rows] = synth.to_bf16_bits(synth.bf16_bits_to_f32(s[rows]) * np.float32(factor)) if s.dtype == np.uint16 \
+        else s[rows] * np.float32(factor)
+    layer[name] = (w, s)
+
+
+def _mlp_case(shared, d, f, T, p_f=None, edit=None):
+    """A layer without heads, whose contribution is scaled above the residual that float32 adds to it."""
+    sh = synth.tiny_shape(d=d, hq=2, hkv=1, dh=64, f=f)
+    layer = synth.layer_weights(sh, 0, quant="group" if shared else "row")
+    _scale(layer, "wd", 64.0)
+    if edit:
+        edit(layer)
+    q, kv, ff = synth.all_kept_mask(sh) if p_f is None else synth.raw_mask(sh, 3, p_f=p_f, block=16 if shared else 1)
+    q[:] = 0
+    return PrefillCase(sh, (q, kv, ff), T, 0, store=[layer], shared=shared)
+
+
+def _errors(case, but=()):
+    """Per token: error of the layer's contribution over the contribution, columns `but` left out."""
+    got, want = (np.delete(y - case.x, but, axis=1) for y in (case.run(), case.oracle()))
+    return np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+
+
+TILE_CASES = [(False, 528, 2000, 0.6, T, dict(gateup=(2, 1, 0, 0), down=(2, 5, 0, 0))) for T in (1, 31, 32, 33)] + \
+    [(False, 528, 12400, 0.6, T, dict(gateup=(1, 1, 0, 0), down=(3, ks, 0, 0))) for T, ks in ((65, 8), (127, 5), (129, 5))] + \
+    [(False, 528, 13200, 0.97, T, dict(gateup=(0, 1, 0, 0), down=(3, ks, 0, 0))) for T, ks in ((193, 4), (255, 3), (513, 3))] + \
+    [(False, 1168, 2000, 0.6, T, dict(gateup=(3, 1, 0, 0), down=(2, 5, 0, 0))) for T in (31, 32, 65)] + [
+        (False, 528, 6160, 0.97, 600, dict(gateup=(0, 1, 0, 0), down=(3, 1, 0, 0))),
+        (False, 2064, 1040, 0.97, 640, dict(gateup=(4, 1, 0, 0), down=(4, 1, 0, 0))),
+        (False, 2064, 1040, 0.97, 705, dict(gateup=(4, 1, 0, 0), down=(1, 1, 0, 0))),
+        (False, 4112, 2064, 0.97, 33, dict(gateup=(3, 1, 0, 0), down=(1, 8, 0, 0))),
+        (False, 4096, 544, 0.97, 1025, dict(gateup=(4, 1, 0, 0), down=(0, 1, 0, 0))),
+        (False, 4096, 9216, 0.97, 580, dict(gateup=(1, 1, 0, 0), down=(0, 3, 0, 0))),
+        (True, 512, 12288, 0.97, 31, dict(gateup=(2, 1, 0, 0), down=(3, 8, 0, 0))),
+        (True, 512, 8192, 0.97, 33, dict(gateup=(1, 1, 0, 0), down=(3, 8, 0, 0))),
+        (True, 512, 8192, 0.97, 127, dict(gateup=(1, 1, 0, 0), down=(3, 8, 0, 0))),
+        (True, 512, 16384, 0.97, 200, dict(gateup=(0, 1, 0, 0), down=(3, 4, 0, 0))),
+        (True, 512, 16384, 0.97, 255, dict(gateup=(0, 1, 0, 0), down=(3, 4, 0, 0))),
+        (True, 640, 2048, 0.6, 31, dict(gateup=(3, 1, 0, 0), down=(2, 8, 0, 0))),
+        (True, 640, 2048, 0.6, 33, dict(gateup=(3, 1, 0, 0), down=(2, 8, 0, 0))),
+        (True, 1152, 12800, 0.6, 63, dict(gateup=(4, 1, 0, 0), down=(3, 7, 0, 0))),
+        (True, 1024, 8192, 0.97, 129, dict(gateup=(1, 1, 0, 0), down=(4, 8, 0, 0))),
+        (True, 8192, 1536, 0.97, 5, dict(gateup=(3, 1, 0, 0), down=(1, 6, 0, 0))),
+        (True, 8192, 512, 0.97, 1023, dict(gateup=(3, 1, 0, 0), down=(0, 1, 0, 0))),
+        (True, 7168, 10752, 0.99, 330, dict(gateup=(0, 1, 0, 0), down=(0, 3, 0, 0)))]
+
+
+@pytest.mark.parametrize("shared,d,f,p_f,T,launches", TILE_CASES)
+def test_tile_shapes(shared, d, f, p_f, T, launches):
+    """Every tile shape, with and without K splits, at token counts around its tiles, with per-channel
+    masks (rows and K of no alignment) or, from the store, channel blocks of 16 (chunks partly kept)."""
+    print(f"case digits tiles shared={shared} d={d} f={f} T={T}", flush=True)
+    case = _mlp_case(shared, d, f, T, p_f)
+    _takes(case, **launches)
+    rel = _errors(case)
+    print(f"  relative error: largest {rel.max():.2e}, median {np.median(rel):.2e}", flush=True)
+    assert rel.max() < REL_MLP
+
+
 @pytest.mark.parametrize("T", [1, 31, 32, 33, 64, 65, 128, 129, 300])
 def test_token_remainders(T):
-    """Token counts around the 32-, 64- and 128-token tiles; width 528 and a per-channel mask leave
-    K and N without any alignment beyond 16, and every projection splits K where T is small."""
+    """A whole layer at token counts around the tiles (32 x 128 here) and the attention's blocks; width
+    528 and a per-channel mask leave K and N without any alignment beyond 16; QKV and down split K."""
     print(f"case digits T={T}", flush=True)
     sh = synth.tiny_shape(d=528, hq=6, hkv=3, dh=64, f=2000)
     case = _case(sh, T, pos0=7)
+    _takes(case, qkv=(2, 2, 0, 0), o=(2, 1, 0, 0), gateup=(2, 1, 0, 0), down=(2, 5, 0, 0))
     assert _rel(case.run(), case.oracle()) < REL
 
 
 @pytest.mark.parametrize("d,hq,hkv,dh,f,T", [(16, 1, 1, 64, 16, 5),        # one chunk, mostly padding
                                              (128, 2, 1, 128, 144, 40),
                                              (1040, 8, 8, 128, 8208, 70),   # long ragged down rows
-                                             (4096, 32, 8, 128, 4096, 520)])   # 128 x 256 tiles
+                                             (1152, 4, 2, 64, 13056, 120),
+                                             (384, 4, 2, 64, 640, 20),
+                                             (4096, 32, 8, 128, 4096, 520)])
 def test_widths(d, hq, hkv, dh, f, T):
     print(f"case digits d={d} hq={hq} hkv={hkv} dh={dh} f={f} T={T}", flush=True)
     case = _case(synth.tiny_shape(d=d, hq=hq, hkv=hkv, dh=dh, f=f), T)
     assert _rel(case.run(), case.oracle()) < REL
 
 
-@pytest.mark.parametrize("shared,d,f,T", [(False, 4096, 8192, 600), (True, 4096, 8192, 600), (True, 8192, 2048, 1200)])
-def test_cut_launch(shared, d, f, T):
+@pytest.mark.parametrize("shared,d,f,T,launches", [(False, 4096, 8192, 600, dict(gateup=(0, 1, 512, 4))),
+                                                   (True, 8192, 2048, 1060, dict(down=(0, 1, 1024, 3))),
+                                                   (True, 8192, 2048, 1088, dict(down=(0, 1, 1024, 3)))])
+def test_cut_launch(shared, d, f, T, launches):
     """Token counts at which a projection is cut in two launches (whole rounds of 128 x 256 tiles, then
-    smaller ones): gate/up with about 7950 channels at 600 tokens, and the column-mapped down
-    projection of 8192 rows at 1200 tokens, whose chunk list stays behind the first launch's first
-    token."""
+    smaller ones): gate/up with about 7950 channels, and the column-mapped down projection of 8192
+    rows, whose chunk list serves both launches."""
     print(f"case digits cut shared={shared} d={d} f={f} T={T}", flush=True)
     sh = synth.tiny_shape(d=d, hq=4, hkv=2, dh=64, f=f)
-    case = PrefillCase(sh, synth.raw_mask(sh, 3, p_f=0.97, block=16), T, 0, shared=shared)
+    mask = synth.raw_mask(sh, 3, p_f=0.97, block=16)
+    case = PrefillCase(sh, mask, T, 0, shared=shared)
+    _takes(case, **launches)
     assert _rel(case.run(), case.oracle()) < REL
+    mlp = _mlp_case(shared, d, f, T, 0.97)
+    _takes(mlp, **launches)
+    assert _errors(mlp).max() < REL_MLP
 
 
-@pytest.mark.parametrize("shared", [False, True])
-@pytest.mark.parametrize("d,f,T", [(384, 640, 20),        # three chunks for four groups
-                                   (640, 12800, 20),      # 32 x 64 tiles, one row tile of tokens
-                                   (1152, 12800, 33),     # nine chunks; a second, nearly empty token tile
-                                   (1152, 13056, 120)])   # 64 x 128 tiles, nine chunks over two groups
-def test_chunk_groups(shared, d, f, T):
+@pytest.mark.parametrize("shared,d,f,T,launches", [
+    (False, 640, 12800, 20, dict(down=(3, 8, 0, 0))),      # four groups: splits of seven and eight chunks
+    (False, 1152, 12800, 33, dict(down=(3, 6, 0, 0))),     # a second, nearly empty token tile
+    (False, 2048, 1152, 700, dict(gateup=(4, 1, 0, 0))),   # two groups
+    (True, 384, 640, 20, dict(gateup=(3, 1, 0, 0), down=(3, 2, 0, 0))),   # three chunks for four groups
+    (True, 640, 12800, 20, dict(gateup=(3, 1, 0, 0), down=(3, 7, 0, 0))),
+    (True, 1152, 12800, 33, dict(gateup=(4, 1, 0, 0), down=(3, 7, 0, 0))),    # nine chunks over two groups
+    (True, 1152, 13056, 120, dict(down=(3, 3, 0, 0))),
+    (True, 1152, 2048, 700, dict(down=(4, 2, 0, 0)))])
+def test_chunk_groups(shared, d, f, T, launches):
     """Tiles whose chunks are dealt to groups of waves (short prompts, and up to one workgroup per CU):
     chunk counts that are no multiple of the groups, and fewer chunks than groups."""
     print(f"case digits groups shared={shared} d={d} f={f} T={T}", flush=True)
     sh = synth.tiny_shape(d=d, hq=4, hkv=2, dh=64, f=f)
     case = PrefillCase(sh, synth.raw_mask(sh, 4, p_f=0.6, block=16), T, 3, shared=shared)
+    _takes(case, **launches)
     assert _rel(case.run(), case.oracle()) < REL
 
 
 def test_number_range():
-    """Rows of zeros, of tiny and of large values, and rows with one value far above the rest: each
-    token has its own scale, so a token's result does not depend on its neighbours, and its error
-    stays relative to its own result."""
+    """A whole layer with rows of zeros, of tiny and of large values, and rows with one value far above the
+    rest (most of whose result is the residual; their contributions: the next test and the last)."""
     print("case digits number range", flush=True)
     sh = synth.tiny_shape(d=512, hq=8, hkv=2, dh=64, f=1536)
     case = _case(sh, 8)
@@ -92,6 +178,29 @@ def test_number_range():
     for t in (0, 2, 3, 4, 5, 6, 7):
         assert _rel(got[t], want[t]) < REL, t
     assert np.abs(got[1] - want[1]).max() <= REL * max(1.0, np.abs(want[1]).max())
+
+
+def test_number_range_contributions():
+    """Rows of zeros, of small and of large values, and rows of one value: each token has its own scale,
+    so a token's result does not depend on its neighbours, and its error stays relative to its own
+    contribution. (What is added to a residual of 32 is off by about 2^-25 of that, a few 1e-7 of the
+    contribution.)"""
+    print("case digits number range", flush=True)
+    case = _mlp_case(False, 512, 1536, 8)
+    x = case.x.copy()
+    x[1] = 0.0
+    x[2] *= 1e-6                                           # (a normed input of 3e-4: under the norm's epsilon)
+    x[3] *= 32.0
+    x[4, :] = 0.0
+    x[4, 9] = -2.5
+    x[5, :] = 0.0
+    x[5, 100:103] = (1e-3, 2.0, -1e-2)
+    case.x, case.xd = x, torch.from_numpy(x).cuda()
+    got, want = case.run(), case.oracle()
+    assert np.array_equal(got[1], np.zeros(512)) and not want[1].any()
+    rel = np.linalg.norm(got - want, axis=1)[[0, 2, 3, 4, 5, 6, 7]] / np.linalg.norm(want - x, axis=1)[[0, 2, 3, 4, 5, 6, 7]]
+    print("  relative error:", rel, flush=True)
+    assert rel.max() < REL_MLP
 
 
 def test_non_finite_rows():
@@ -126,54 +235,47 @@ def test_groupwise_store(dh, T):
     assert _rel(case.run(), case.oracle()) < REL
 
 
-@pytest.mark.parametrize("what", ["no_heads", "no_ffn", "wide"])
+@pytest.mark.parametrize("what", ["no_heads", "no_ffn", "wide", "splits", "rows"])
 def test_groupwise_store_edges(what):
-    """Empty modules, and the 128 x 256 tile shape with K splits."""
+    """Empty modules, and whole layers of 64 x 128 tiles, of 128 x 256 tiles with K splits (down), and of
+    8192 rows."""
     print(f"case digits groupwise {what}", flush=True)
-    wide = what == "wide"
-    sh = synth.tiny_shape(d=4096 if wide else 256, hq=8, hkv=2, dh=128 if wide else 64, f=8192 if wide else 512)
-    q, kv, f = synth.raw_mask(sh, 22, p_f=0.7, block=16)
+    d, dh, f, T, p_f, launches = dict(
+        wide=(4096, 128, 8192, 520, 0.7, dict(qkv=(4, 4, 0, 0), o=(1, 1, 0, 0), gateup=(1, 1, 0, 0), down=(1, 1, 0, 0))),
+        splits=(7168, 128, 10752, 330, 0.9, dict(qkv=(4, 7, 0, 0), o=(1, 1, 0, 0), gateup=(1, 1, 0, 0), down=(0, 3, 0, 0))),
+        rows=(8192, 64, 2048, 1200, 0.97, dict(gateup=(4, 1, 0, 0), down=(4, 1, 0, 0)))).get(what, (256, 64, 512, 33, 0.7, {}))
+    sh = synth.tiny_shape(d=d, hq=8, hkv=2, dh=dh, f=f)
+    q, kv, f = synth.raw_mask(sh, 22, p_f=p_f, block=16)
     if what == "no_heads":
         q[:] = 0
     elif what == "no_ffn":
         f[:] = 0
-    case = PrefillCase(sh, (q, kv, f), 520 if wide else 33, 0, shared=True)
+    case = PrefillCase(sh, (q, kv, f), T, 0, shared=True)
+    _takes(case, **launches)
     assert _rel(case.run(), case.oracle()) < REL
 
 
 def _outlier_case(shared, d, f, T, ratio, where, some):
-    """A layer without heads (no rounding of k and v between the input and the result) whose outputs do
-    not use the columns with the outliers. where "x": column 3 of the tokens in `some` is `ratio` times the
-    rms of the others, and no gate or up row reads it; "h": channel 5's up row is `ratio` times the
-    others', and the down projection does not read it. The scales make the layer's own contribution
-    larger than the residual, which float32 adds to it."""
-    sh = synth.tiny_shape(d=d, hq=2, hkv=1, dh=64, f=f)
-    layer = synth.layer_weights(sh, 0, quant="group" if shared else "row")
+    """A layer without heads whose outputs do not use the columns with the outliers. where "x": column 3 of
+    the tokens in `some` is `ratio` times the rms of the others, and no gate or up row reads it; "h":
+    channel 5's up row is `ratio` times the others', and the down projection does not read it."""
+    def edit(layer):
+        def drop(name, column):
+            w = layer[name][0].copy()
+            w[:, column] = 0
+            layer[name] = (w, layer[name][1])
 
-    def scale(name, factor, rows=slice(None)):
-        w, s = layer[name]
-        s = s.copy()
-        s[rows] = synth.to_bf16_bits(synth.bf16_bits_to_f32(s[rows]) * np.float32(factor)) if shared else s[rows] * np.float32(factor)
-        layer[name] = (w, s)
+        if where == "x":
+            # the RMS of a row with the outlier is ratio / sqrt(d)
+            up = 2.0 ** max(0, round(np.log2(ratio / np.sqrt(d))))
+            for n in ("wg", "wu"):
+                _scale(layer, n, up)
+                drop(n, 3)
+        else:
+            _scale(layer, "wu", 2.0 ** round(np.log2(ratio)), slice(5, 6))
+            drop("wd", 5)
 
-    def drop(name, column):
-        w = layer[name][0].copy()
-        w[:, column] = 0
-        layer[name] = (w, layer[name][1])
-
-    scale("wd", 64.0)
-    if where == "x":
-        # the RMS of a row with the outlier is ratio / sqrt(d)
-        up = 2.0 ** max(0, round(np.log2(ratio / np.sqrt(d))))
-        for n in ("wg", "wu"):
-            scale(n, up)
-            drop(n, 3)
-    else:
-        scale("wu", 2.0 ** round(np.log2(ratio)), slice(5, 6))
-        drop("wd", 5)
-    q, kv, ff = synth.all_kept_mask(sh)
-    q[:] = 0
-    case = PrefillCase(sh, (q, kv, ff), T, 0, store=[layer], shared=shared)
+    case = _mlp_case(shared, d, f, T, edit=edit)
     if where == "x":
         x = case.x.copy()
         x[some, 3] = ratio * np.sign(x[some, 3] + 0.5)
@@ -212,10 +314,7 @@ def test_outlier_rows(shared, d, f, T, launches):
                                ("h", 1e4, every)):
         print(f"case outliers shared={shared} d={d} f={f} T={T} {where} {ratio}", flush=True)
         case = _outlier_case(shared, d, f, T, ratio, where, some)
-        for kind, want in launches.items():
-            assert case.launch(kind) == want
-        # (the outlier's own column holds it in float32 beside the layer's result)
-        got, want = (np.delete(y - case.x, 3, axis=1) for y in (case.run(), case.oracle()))
-        rel = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+        _takes(case, **launches)
+        rel = _errors(case, but=(3,))         # (the outlier's own column holds it beside the layer's result)
         print(f"  relative error: largest {rel.max():.2e}, median {np.median(rel):.2e}", flush=True)
         assert rel.max() < 2e-5, (where, ratio, int(rel.argmax()))
