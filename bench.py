@@ -720,7 +720,7 @@ def bench_prefill(args, wl):
     line = {
         "metric": METRIC, "value": round(sp["ms"], 5), "unit": "ms/prefill", "n_gpus": 1,
         "steps": sp["steps"], "warmup": args.warmup, "ms_per_step": round(sp["ms"], 5),
-        "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "bf16x2-mfma",
+        "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "int8w-int8x3-f32",
         "data": "synthetic",
         "config": {"workload": wl.name, "d_model": sh.d_model, "n_q_heads": sh.n_q_heads,
                    "n_kv_heads": sh.n_kv_heads, "head_dim": sh.head_dim, "d_ffn": sh.d_ffn,

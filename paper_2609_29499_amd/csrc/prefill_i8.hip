@@ -9,7 +9,7 @@
 // the token's largest activation. Against an operand pair of hi and lo BF16 (about 2^-19 of each
 // activation, on the BF16 matrix cores) the error of a random token is lower (rms 2^-22
 // of the token's rms for a largest value of 4 to 5 rms), and the issued matrix work is three
-// INT8 passes (3 / 3.3 POP/s measured) instead of two BF16 passes (2 / 1.8 PFLOP/s measured).
+// INT8 passes instead of two BF16 passes at half the rate.
 //
 // Rows with outliers. Beside a value far above the rest one scale leaves the rest fewer bits than a
 // hi/lo pair does (with one value 1000 times the rms of 4096 others, an output that does not use that
@@ -40,18 +40,15 @@
 // scale, then d0 (five vector operations per output and chunk next to 48 matrix operations per 64
 // outputs and lane). Rows come through the plan's row map; a column-mapped operand is laid out in
 // the store's own chunks, those with any retained column (listed by the operand's writer), dropped
-// columns zero. It replaced four
-// passes of hi/lo weights times hi/lo activations on the BF16 matrix cores: one 8B layer at 1000
-// tokens 998 -> 548 us.
+// columns zero. It replaced four passes of hi/lo weights times hi/lo activations on the BF16 matrix
+// cores: one 8B layer at 1000 tokens 1005 -> 586 us.
 //
-// What bounds it: power. At a full chip of 128 x 256 tiles the clock falls from 2.4 to 1.6-1.8 GHz
-// (cycle against real-time counters), a chunk of 64 takes about 2100 cycles of which 1536 are
-// matrix cycles, and the matrix cores alone on random registers reach 3.3 POP/s of the nominal 5.
-// What saves energy therefore saves time: chunks of whole 128-byte lines instead of halves of them
-// (12 % more cycles, a 15 % higher clock), 32 x 128 outputs per wave instead of 64 x 64 (fewer LDS
-// reads per product, 4 %). With the loads left out (a copy of the kernel) the 2 x 16384 x 8192
-// gate/up projection at 2048 tokens takes 960 instead of 1300 us; on the BF16 matrix cores with
-// hi/lo operands it took 2240 us.
+// What bounds it. Large calls: the matrix cores at the clock they leave. The 2 x 16384 x 8192 gate/up
+// projection at 2048 tokens (1.29 ms; hi/lo operands on the BF16 matrix cores took 2.24) keeps them busy
+// 64 % of its cycles at a clock of 1.80 GHz, of 2.4 nominal; one round of 128 x 256 tiles (8B gate/up
+// at 512 tokens) 53 % at 2.01 GHz. The LDS serves reads for 41 % of the cycles, half of that in conflicts
+// that the swizzle leaves. Chunks are whole 128-byte lines, and a wave's tile is 32 x 128 rather than
+// 64 x 64, which needs fewer fragment reads per product. Short prompts: the latency of a chunk (KW below).
 #include <algorithm>
 #include <type_traits>
 
@@ -83,7 +80,7 @@ __device__ __forceinline__ void stage_done() {
 }
 
 // LDS slot of 16-byte piece p of row `row` (rows of kKC bytes): any 8 consecutive rows read at one
-// piece meet distinct banks
+// piece meet distinct 16-byte columns
 __device__ __forceinline__ int slot(int row, int p) { return p ^ (row & 7); }
 
 // eight INT8 values (exact in BF16) as a matrix operand, and an operand of the LDS
@@ -361,7 +358,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KW, WAVES) void pf_i8_kernel(PfI8A
   constexpr int ND = SH ? 1 : 3, QG = 4 / KW;           // digits, groups of four outputs per wave group
   constexpr int QS = KW == 2 ? 2 : 4;                   // groups of four a wave leaves (KW 4: its own unused)
   constexpr size_t kSumBytes = KW > 1 ? size_t(KW) * NW * NT * QS * kWave * 16 : 0;   // of one digit
-  static_assert((ND > 1 ? 2 : 1) * kSumBytes <= sizeof(st0) && kSumBytes + TM * 4 <= sizeof(st1), "the sums fit the stages");
+  static_assert((ND > 1 ? 2 : 1) * kSumBytes <= sizeof(st0) && kSumBytes <= sizeof(st1), "the sums fit the stages");
   auto sums = [&](int d, int k, int nt, int g) -> i32x4* {
     char* base = d < 2 ? reinterpret_cast<char*>(&st0) + size_t(d) * kSumBytes : reinterpret_cast<char*>(&st1);
     return reinterpret_cast<i32x4*>(base) + (((k * NW + wave) * NT + nt) * QS + g % QS) * kWave + lane;
