@@ -184,7 +184,8 @@ tasp_status tasp_shared_plan_workspace_bytes(const tasp_model_desc* desc, size_t
  * paper's channel groups are 1,024 wide). Such a plan serves every call a per-row plan serves
  * (decode at batch 1..max_batch, prefill, tasp_generate, tasp_serve_turn, the profiling calls),
  * reading the store in place: batch 1 with per-lane group scales, batches and prefill on the
- * matrix cores with each weight times its group scale split exactly into BF16 hi and lo parts;
+ * matrix cores, a group's sum times its scale (batches where 128 retained columns are not one group:
+ * each weight times its scale, split exactly into BF16 hi and lo parts);
  * only tasp_plan_panel returns TASP_ERR_UNSUPPORTED (there are no panels). Its signature differs
  * from a per-row plan of the same mask, so caches are not shared between the two formats.
  * `workspace` (256-byte aligned, plan_bytes) holds the plan's metadata. `scratch` (256-byte

@@ -17,6 +17,7 @@ import pytest
 import torch
 
 import synth
+from paper_2609_29499_amd import session as S
 from tests.gpu_case import PrefillCase
 
 pytestmark = pytest.mark.gpu
@@ -318,3 +319,24 @@ def test_outlier_rows(shared, d, f, T, launches):
         rel = _errors(case, but=(3,))         # (the outlier's own column holds it beside the layer's result)
         print(f"  relative error: largest {rel.max():.2e}, median {np.median(rel):.2e}", flush=True)
         assert rel.max() < 2e-5, (where, ratio, int(rel.argmax()))
+
+
+def test_outlier_rows_under_capture():
+    """Which rows are pairs is decided on the device: a captured prefill serves inputs with outliers in
+    other tokens, in all and in none, with the bits of an eager call."""
+    print("case outliers captured", flush=True)
+    case = _outlier_case(False, 512, 6144, 330, 1000.0, "x", np.arange(0, 330, 7))
+    first = case.run()
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        case.plan.prefill(case.xd, case.T, case.cache, 0, case.out, stream=S.current_stream())
+    for step in (7, 1, 330, 5, 7):
+        x = torch.from_numpy(synth.activations(330, 512, step)).cuda()
+        x[::step, 3] = -1000.0 if step < 330 else 0.5
+        case.xd.copy_(x if step != 7 else torch.from_numpy(case.x).cuda())
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = case.out.cpu().numpy().astype(np.float64)
+        assert np.array_equal(replayed, case.run()), step
+        assert step != 7 or np.array_equal(replayed, first)
